@@ -21,10 +21,20 @@ constexpr int32_t kErrFrontierId = 8, kErrFlagId = 16, kErrFirstPosNeg = 32, kEr
                   kErrNewNode = 128, kErrEmit = 256;
 constexpr int32_t kErrInternal = 8 | 16 | 32 | 64 | 128 | 256;
 
-// frontier nodes by degree: 0: deg <= 16, 1: <= 32, 2: <= 64 (lane groups of 4, 8, 16, four
-// slots per lane), 3: <= kHubDegree (one wavefront), 4: hubs (one workgroup)
-constexpr int kNumBins = 5;
-constexpr uint32_t kHubDegree = 4096;
+// Frontier nodes by degree.  0: deg <= 16, 1: <= 32 (groups of 4, 8 lanes, four slots per lane);
+// 2: <= 64, 3: <= 128, ... 7: <= kGroupDegree (groups of 16 lanes, 64 slots per step; a wavefront's
+// four nodes come from one bin, so their rows differ at most twofold); 8: one
+// wavefront each; 9: hubs (one workgroup each; the host says from which degree on).  A hop that the 16-lane groups do not serve puts the
+// nodes of bins 3-7 into bin 8.
+constexpr int kNumBins = 10;
+constexpr int kWideBin = 8, kHubBin = 9;
+constexpr uint32_t kGroupDegree = 2048;
+// Two bins share an array of as many records as a frontier can have nodes: bin b < 5 fills array b
+// from the front, bin b + 5 from the back.
+constexpr int kBinArrays = 5;
+// The bins' counters sit a cache line apart: k_frontier's workgroups reserve space in all of them
+// at once, and atomics on one line queue behind each other.
+constexpr int kBinCountStride = 32;
 
 // Counts of the running call, written by kernels, copied to the host by the last kernel.
 struct DevState {
@@ -35,8 +45,7 @@ struct DevState {
   int32_t n_radix;  // nodes that went through the exhaustive selection path
   int32_t n_deferred[2];  // weighted calls: wide nodes / hubs that the first launch of a hop left to the second
   int32_t class_mix;  // weighted calls: bit 0 some node is cached, bit 1 some node is not
-  // scratch of the running hop; zero between hops and between calls
-  int32_t bin_count[kNumBins];  // the degree bins
+  int32_t left_small;  // scratch of the running hop: the first launch marked a node of bin 2
 };
 
 // What k_sample needs to know of a frontier node; k_frontier has it all in registers and writes
@@ -50,6 +59,11 @@ struct NodeRec {
   int32_t local_off;  // edges of earlier nodes of the same scan tile
   int32_t left;       // set by the first sampling launch of a weighted hop: the second launch samples this node
 };
+
+// record `pos` of a bin, given the bins' first records
+__device__ __forceinline__ NodeRec* bin_rec(NodeRec* const* first, int bin, int64_t pos) {
+  return bin < kBinArrays ? first[bin] + pos : first[bin] - pos;
+}
 
 // ---------------------------------------------------------------------------
 // block-wide helpers (256 threads = 4 waves)

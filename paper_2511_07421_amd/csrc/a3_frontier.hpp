@@ -81,12 +81,18 @@ struct FrontierArgs {
   int32_t fanout;
   int32_t* tile_sums;
   int64_t num_nodes;
-  NodeRec* bins[kNumBins];   // node records per degree bin
+  NodeRec* bins[kNumBins];   // first record of every degree bin (see bin_rec)
+  int32_t* bin_count;        // [kNumBins * kBinCountStride], zero between hops and between calls
+  int32_t groups;            // bins 3-7 are in use
+  uint32_t hub_degree;       // rows longer than this are hubs
   const int32_t* class_mix_kept;  // hop 0 of a weighted call that reuses the bitmap of cached nodes, else null
 };
 
-__device__ __forceinline__ int degree_bin(uint32_t deg) {
-  return deg <= 16 ? 0 : deg <= 32 ? 1 : deg <= 64 ? 2 : deg <= kHubDegree ? 3 : 4;
+__device__ __forceinline__ int degree_bin(uint32_t deg, bool groups, uint32_t hub_degree) {
+  if (deg <= 16) return 0;
+  if (deg > hub_degree) return kHubBin;
+  if (deg > kGroupDegree || (deg > 64 && !groups)) return kWideBin;
+  return 28 - __clz((int)(deg - 1));  // 17..32: 1, 33..64: 2, ... 1025..2048: 7
 }
 
 // The launch is sized for a bound on the frontier; workgroups past its real size leave at once.
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(kTileThreads) void k_frontier(const FrontierArgs<Id
         deg = 0;
       }
       cnt[k] = deg < (int64_t)a.fanout ? (uint32_t)deg : (uint32_t)a.fanout;
-      bin[k] = degree_bin((uint32_t)deg);
+      bin[k] = degree_bin((uint32_t)deg, a.groups != 0, a.hub_degree);
       sum += cnt[k];
       rec[k].v = v;
       rec[k].row = row;
@@ -190,12 +196,12 @@ __global__ __launch_bounds__(kTileThreads) void k_frontier(const FrontierArgs<Id
   // one global reservation per bin and block, then scatter the node records
   if (threadIdx.x < kNumBins)
     bin_base[threadIdx.x] = bin_n[threadIdx.x]
-                                ? (uint32_t)atomicAdd(&a.st->bin_count[threadIdx.x], (int32_t)bin_n[threadIdx.x])
+                                ? (uint32_t)atomicAdd(&a.bin_count[threadIdx.x * kBinCountStride], (int32_t)bin_n[threadIdx.x])
                                 : 0u;
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kTilePerThread; ++k)
-    if (bin[k] >= 0) a.bins[bin[k]][bin_base[bin[k]] + rank_in_bin[k]] = rec[k];
+    if (bin[k] >= 0) *bin_rec(a.bins, bin[k], (int64_t)bin_base[bin[k]] + rank_in_bin[k]) = rec[k];
   if (threadIdx.x == 0) a.tile_sums[blockIdx.x] = (int32_t)total;
 }
 

@@ -7,8 +7,9 @@
 //                 tile sums, node records binned by degree
 //   k_scan_tiles  exclusive scan of the tile sums (one workgroup; only above 1024 tiles,
 //                 otherwise the consumers scan the tile sums themselves in LDS)
-//   k_sample      keyed selection; small-degree bins by groups of 4/8/16 lanes, wide nodes one
-//                 wavefront each, hubs one workgroup each; records first occurrences in node_map.
+//   k_sample      keyed selection; nodes of up to 2048 neighbours by groups of 4, 8 or 16 lanes,
+//                 wide ones by one wavefront each, hubs by one workgroup each (in small frontiers all
+//                 above 64 neighbours by a wavefront or workgroup); records first occurrences in node_map.
 //                 Three instances: all weights equal; the first launch of a weighted hop (decides
 //                 a node from its best draws where enough of them are cached, marks the others);
 //                 the full weighted sampler (second launch, for the marked nodes)

@@ -85,6 +85,7 @@ struct RelabelArgs {
   const int32_t* tile_sums;
   int64_t cap_tiles;         // the launch's bound on the tiles in use (at most the entries of tile_sums)
   DevState* st;
+  int32_t* bin_count;        // the degree bins' counters, cleared for the next hop
   int32_t hop;
   int32_t last_hop;          // this hop ends the call
   int64_t num_nodes;
@@ -106,8 +107,10 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
   if (fuse) sums = tile_sums_load(a.tile_sums, a.cap_tiles);  // does not wait for the counts
   const int64_t n = a.st->n_edges[a.hop];
   const int32_t n_dst = a.st->n_dst[a.hop];
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    for (int b = 0; b < kNumBins; ++b) a.st->bin_count[b] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kNumBins) {
+    a.bin_count[threadIdx.x * kBinCountStride] = 0;
+    if (threadIdx.x == 0) a.st->left_small = 0;
+  }
   // a workgroup past the hop's edges leaves; workgroup 0 stays in any case: it publishes the
   // hop's source count
   if (blockIdx.x != 0 && (int64_t)blockIdx.x * kRelabelPerThread * kTileThreads >= n) return;

@@ -22,14 +22,18 @@ struct SampleArgs {
   int32_t* node_map;         // global id -> map_base + (first position / local id)
   int32_t map_base;
   DevState* st;
-  NodeRec* bins[kNumBins];   // kWeightedFast sets `left` in the records of bins 3, 4 that it leaves to the second launch
+  NodeRec* bins[kNumBins];   // kWeightedFast sets `left` in the records that it leaves to the second launch
+  const int32_t* bin_count;  // [kNumBins * kBinCountStride]
   uint32_t left_only;        // kWeightedFull as a second launch: only the records with `left` set
   int64_t num_nodes;
   int64_t cap_edges;         // entries in gid / eids (arena capacity of this hop)
-  uint32_t role_blocks[5];   // workgroups serving bins 0, 1, 2 (lane groups), 3 (wide), 4 (hubs)
+  uint32_t hub_blocks;       // workgroups serving the hubs, the wide nodes (one wavefront each),
+  uint32_t wide_blocks;      // and the lane groups (bins 0-7)
+  uint32_t group_blocks;
   int32_t hop;
   int32_t fanout;
   uint32_t lambda;    // expected number of candidates kept by the draw threshold
+  uint32_t group_lambda;  // the same for the 16-lane groups
   uint32_t cap;       // candidate buffer entries per wavefront (>= lambda)
   uint32_t xcap;      // challenger buffer entries (weighted only, multiple of 64, >= 128)
   uint32_t capb;      // second candidate list (weighted only; 0: rescan the row instead)
@@ -49,7 +53,20 @@ __device__ __forceinline__ bool is_cached(const SampleArgs<IdxT>& a, int64_t u) 
   return u >= 0 && u < a.num_nodes && ((a.cached_bits[u >> 5] >> (u & 31)) & 1u);
 }
 
-// writes one sampled edge
+// Writes sampled edge e of the hop: neighbour g, found at CSR position eid.
+template <typename IdxT>
+__device__ __forceinline__ void put_edge(const SampleArgs<IdxT>& a, int32_t n_dst, int32_t e, int64_t eid, IdxT g) {
+  // a neighbour id outside the graph or an offset outside the arena is dropped, never written
+  if (e < 0 || (int64_t)e >= a.cap_edges || (int64_t)g < 0 || (int64_t)g >= a.num_nodes) {
+    atomicOr(&a.st->error, kErrEmit);
+    return;
+  }
+  a.gid[e] = g;
+  if (a.eids) a.eids[e] = eid;
+  atomicMin(&a.node_map[(int64_t)g], a.map_base + n_dst + e);
+}
+
+// writes one sampled edge of a node, given its slot
 template <typename IdxT>
 struct Emitter {
   const SampleArgs<IdxT>& a;
@@ -58,16 +75,7 @@ struct Emitter {
   int32_t n_dst;
   __device__ __forceinline__ void operator()(uint32_t pos, uint32_t slot) const {
     const int64_t eid = row + slot;
-    const IdxT g = a.indices[eid];
-    const int32_t e = base + (int32_t)pos;
-    // a neighbour id outside the graph or an offset outside the arena is dropped, never written
-    if (e < 0 || (int64_t)e >= a.cap_edges || (int64_t)g < 0 || (int64_t)g >= a.num_nodes) {
-      atomicOr(&a.st->error, kErrEmit);
-      return;
-    }
-    a.gid[e] = g;
-    if (a.eids) a.eids[e] = eid;
-    atomicMin(&a.node_map[(int64_t)g], a.map_base + n_dst + e);
+    put_edge<IdxT>(a, n_dst, base + (int32_t)pos, eid, a.indices[eid]);
   }
 };
 
@@ -78,6 +86,14 @@ struct Emitter {
 //                  case), and is put on a list for a second launch where it is not.  Keeps no
 //                  second candidate list, no rescanning path and so far fewer registers;
 //   kWeightedFull  two weights, every path: the second launch, which serves that list.
+// the lane's index as a value that the compiler cannot trace back: what is computed from it stays where
+// it is used instead of being hoisted out of the node loop and held in registers for its whole length
+__device__ __forceinline__ uint32_t local_lane_id() {
+  uint32_t lane = lane_id();
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 constexpr int kUniform = 0, kWeightedFull = 1, kWeightedFast = 2;
 
 constexpr double kInvOne = 1.0 / 65536.0;  // 1 / weight of an uncached neighbour (Q16.16)
@@ -121,6 +137,20 @@ __device__ __forceinline__ uint32_t draw_floor_for_key(uint64_t BK, uint32_t w_q
   if (xmin <= 0.0) return 0u;
   if (xmin >= 4294967295.0) return 0xFFFFFFFFu;
   return (uint32_t)xmin;
+}
+
+// the record that lane src_lane holds, in scalar registers: what is computed from it is computed
+// once for the wavefront
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t src_lane);
+__device__ __forceinline__ NodeRec readlane_rec(const NodeRec& r, uint32_t src_lane) {
+  NodeRec one;
+  one.v = (int64_t)readlane_u64((uint64_t)r.v, src_lane);
+  one.row = (int64_t)readlane_u64((uint64_t)r.row, src_lane);
+  one.deg = (uint32_t)__builtin_amdgcn_readlane((int32_t)r.deg, (int32_t)src_lane);
+  one.i = __builtin_amdgcn_readlane(r.i, (int32_t)src_lane);
+  one.local_off = __builtin_amdgcn_readlane(r.local_off, (int32_t)src_lane);
+  one.left = 0;
+  return one;
 }
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t src_lane) {
@@ -516,7 +546,7 @@ __device__ __forceinline__ void sample_node_wave(const SampleArgs<IdxT>& a, cons
                                  const NodeRec& r, int32_t n_dst, uint64_t* cand, uint64_t* rest,
                                  bool prefiltered, uint32_t pre_cnt, uint32_t pre_cnt_b,
                                  bool both_classes, int32_t* left) {
-  const uint32_t lane = lane_id();
+  const uint32_t lane = local_lane_id();
   const int64_t v = r.v;
   const int64_t row = r.row;
   const int64_t i = r.i;
@@ -783,113 +813,416 @@ __device__ __forceinline__ void sample_node_wave(const SampleArgs<IdxT>& a, cons
   }
 }
 
-// ---- a group of G lanes (4, 8 or 16), one node of degree <= 4 G: four slots per lane ------------
-// The draws of a lane are one Philox block.  Selection is m rounds of "best remaining slot of
-// the group" (lane-local best, butterfly reduction, lowest lane among equals), which costs
-// O(m log G) instead of ranking every slot against every other.
-template <typename IdxT, int G, int kMode>
-__device__ void sample_node_group(const SampleArgs<IdxT>& a, const int32_t* tile_offs,
-                                  const NodeRec& r, int32_t n_dst, bool both_classes) {
-  const uint32_t lane = lane_id();
-  const uint32_t gl = lane & (G - 1);       // lane inside the group
-  const uint32_t gshift = lane & ~(G - 1);  // first lane of the group inside the wavefront
-  const int64_t v = r.v;
-  const int64_t row = r.row;
-  const int64_t i = r.i;
-  const uint32_t deg = r.deg;  // <= 4 G by construction of the bins
-  const uint32_t f = (uint32_t)a.fanout;
-  const int32_t base = tile_offs[i >> kTileShift] + r.local_off;
-  if (gl == 0) a.blk_indptr[i] = base;
-  const Emitter<IdxT> emit{a, row, base, n_dst};
-  if (deg <= f) {
-    for (uint32_t s = gl; s < deg; s += G) emit(s, s);
+// ---- lanes of a row of 16, without LDS -----------------------------------------------------------
+// __shfl goes through the LDS unit (some hundred cycles a step); a data-parallel move inside a row
+// of 16 lanes is an operand of an ordinary vector instruction.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {  // lanes without a source read 0
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, kCtrl, 0xf, 0xf, true);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;          // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // i -> 7 - i in a half row, i -> 15 - i in a row
+constexpr int kDppShr = 0x110, kDppLast = 0x15F;         // lane i from i - n; every lane from lane 15
+
+__device__ __forceinline__ uint32_t row16_incl_scan(uint32_t v) {
+  v += dpp_u32<kDppShr + 1>(v);
+  v += dpp_u32<kDppShr + 2>(v);
+  v += dpp_u32<kDppShr + 4>(v);
+  v += dpp_u32<kDppShr + 8>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t row16_last(uint32_t v) { return dpp_u32<kDppLast>(v); }
+
+// the largest / smallest value of a group of G lanes, in each of them (after the first two steps a
+// quad agrees, after the third a half row, so a mirror image serves as the exchange)
+template <int G>
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v) {
+  v = max(v, dpp_u32<kDppXor1>(v));
+  v = max(v, dpp_u32<kDppXor2>(v));
+  if (G >= 8) v = max(v, dpp_u32<kDppHalfMirror>(v));
+  return v;
+}
+// the same for the minimum; v must be active in all lanes of the row
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_min_u32(uint32_t v) {
+  return min(v, dpp_u32<kCtrl>(v));
+}
+template <int G>
+__device__ __forceinline__ uint32_t group_min_u32(uint32_t v) {
+  v = dpp_min_u32<kDppXor1>(v);
+  v = dpp_min_u32<kDppXor2>(v);
+  if (G >= 8) v = dpp_min_u32<kDppHalfMirror>(v);
+  if (G >= 16) v = dpp_min_u32<kDppMirror>(v);
+  return v;
+}
+template <int kCtrl>
+__device__ __forceinline__ uint64_t dpp_min_u64(uint64_t v) {
+  const uint64_t other = ((uint64_t)dpp_u32<kCtrl>((uint32_t)(v >> 32)) << 32) | dpp_u32<kCtrl>((uint32_t)v);
+  return other < v ? other : v;
+}
+template <int G>
+__device__ __forceinline__ uint64_t group_min_u64(uint64_t v) {
+  v = dpp_min_u64<kDppXor1>(v);
+  v = dpp_min_u64<kDppXor2>(v);
+  if (G >= 8) v = dpp_min_u64<kDppHalfMirror>(v);
+  return v;
+}
+
+// ---- edges of the lane groups ---------------------------------------------------------------------
+// A group's chosen slots stand in LDS, in order, k of them; consecutive lanes write consecutive edges.
+// All neighbour ids of a group are asked for before the first is used; where one round of the lanes
+// is enough the round is only begun here (`pending`) and written while the wavefront's next nodes are
+// drawn, so that nothing waits for the ids.  ids: the ids themselves stand in LDS too (low words,
+// then, kListIds further on, high words), or null.
+constexpr uint32_t kListIds = 32;
+
+template <typename IdxT>
+struct PendingEdge {
+  int64_t eid;
+  IdxT g;
+  int32_t e;
+  bool on;
+};
+
+template <typename IdxT>
+__device__ __forceinline__ void put_pending(const SampleArgs<IdxT>& a, int32_t n_dst, PendingEdge<IdxT>& p) {
+  if (p.on) put_edge<IdxT>(a, n_dst, p.e, p.eid, p.g);
+  p.on = false;
+}
+
+template <typename IdxT>
+__device__ __forceinline__ IdxT listed_id(const uint32_t* ids, uint32_t j) {
+  if (sizeof(IdxT) == 4) return (IdxT)ids[j];
+  return (IdxT)(((uint64_t)ids[kListIds + j] << 32) | ids[j]);
+}
+
+template <typename IdxT, int G>
+__device__ __forceinline__ void put_list(const SampleArgs<IdxT>& a, int64_t row, int32_t base, int32_t n_dst,
+                                         uint32_t k, const uint32_t* list, const uint32_t* ids,
+                                         PendingEdge<IdxT>& pending) {
+  const uint32_t gl = local_lane_id() & (G - 1);
+  if (__ballot(k > (uint32_t)G) == 0) {
+    pending.on = gl < k;
+    if (pending.on) {
+      pending.eid = row + list[gl];
+      pending.e = base + (int32_t)gl;
+      pending.g = ids ? listed_id<IdxT>(ids, gl) : a.indices[pending.eid];
+    }
     return;
   }
-  const uint32_t m = f;
+  int64_t eid[4];
+  IdxT g[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t j = (uint32_t)(r * G) + gl;
+    if (j < k) {
+      eid[r] = row + list[j];
+      g[r] = ids ? listed_id<IdxT>(ids, j) : a.indices[eid[r]];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t j = (uint32_t)(r * G) + gl;
+    if (j < k) put_edge<IdxT>(a, n_dst, base + (int32_t)j, eid[r], g[r]);
+  }
+}
+
+// ---- a group of G lanes (4 or 8), one node of degree <= 4 G: four slots per lane -----------------
+// The draws of a lane are one Philox block.  Selection is m rounds of "best remaining slot of the
+// group" on 32-bit keys: lane-local minimum, reduction over the group, every slot that has the
+// minimum is out.  Equal keys (weighted: keys that agree in their upper 32 bits) leave more than m
+// chosen; the choice is then made again in full precision, one slot per round, all ties resolved.
+template <typename IdxT, int G, int kMode>
+__device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, const int32_t* tile_offs,
+                                                  const NodeRec& r, bool live, int32_t n_dst, uint32_t* lds,
+                                                  bool both_classes, PendingEdge<IdxT>& pending) {
+  constexpr uint32_t kStride = 4 * G + 4;  // groups start in other banks
+  const uint32_t lane = local_lane_id();
+  const uint32_t gl = lane & (G - 1);       // lane inside the group
+  const uint32_t gshift = lane & ~(G - 1);  // first lane of the group inside the wavefront
+  uint32_t* keys = lds + (lane / G) * kStride;
+  const int64_t v = r.v;
+  const int64_t row = r.row;
+  const uint32_t deg = live ? r.deg : 0;  // <= 4 G by construction of the bins
+  const uint32_t m = (uint32_t)a.fanout;
+  const int32_t base = live ? tile_offs[r.i >> kTileShift] + r.local_off : 0;
+  if (live && gl == 0) a.blk_indptr[r.i] = base;
+  const bool draw = deg > m;  // else every neighbour is kept
   const PhiloxKey pk{(uint32_t)(uint64_t)v, (uint32_t)((uint64_t)v >> 32), (uint32_t)a.hop,
                      a.seed_lo, a.seed_hi};
-  uint32_t x[4];
-  philox4x32_10(gl, pk, x);
-  uint32_t alive = 0;  // bit w: slot 4 gl + w exists and is not chosen yet
+  uint32_t chosen = 0;  // bit w: slot 4 gl + w
 #pragma unroll
-  for (int w = 0; w < 4; ++w) alive |= (4u * gl + w < deg) ? (1u << w) : 0u;
-  uint64_t K[4] = {0, 0, 0, 0};
-  if (kMode != kUniform && both_classes) {
-    bool cached[4];
-    bool any_c = false, any_u = false;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      cached[w] = false;
-      if (alive & (1u << w)) {
-        const int64_t u = (int64_t)a.indices[row + 4u * gl + w];
-        cached[w] = is_cached(a, u);
-        any_c |= cached[w];
-        any_u |= !cached[w];
-      }
-    }
-    // keys are needed only when the group's neighbourhood mixes both classes (otherwise K is
-    // monotone in x and the order is "larger draw first")
-    const uint64_t mc = __ballot(any_c), mu = __ballot(any_u);
-    const uint64_t gmask = ((G == 64) ? ~0ull : ((1ull << G) - 1ull)) << gshift;
-    const bool mixed = (mc & gmask) != 0 && (mu & gmask) != 0;
-    if (mixed) {
+  for (int w = 0; w < 4; ++w) chosen |= (4u * gl + w < deg) ? (1u << w) : 0u;
+  const uint64_t lower_lanes = ((1ull << gl) - 1ull) << gshift;  // of the group
+  if (__ballot(draw)) {
+    const uint32_t alive = draw ? chosen : 0u;
+    uint32_t x[4];
+    philox4x32_10(gl, pk, x);
+    put_pending<IdxT>(a, n_dst, pending);
+    const uint64_t group_lanes = ((1ull << G) - 1ull) << gshift;
+    bool cached[4] = {false, false, false, false};
+    bool mixed = false;
+    if (kMode != kUniform && both_classes) {
+      IdxT u[4];
 #pragma unroll
       for (int w = 0; w < 4; ++w)
-        if (alive & (1u << w))
-          K[w] = sample_key(x[w], cached[w] ? a.bias_q16 : 65536u, cached[w] ? a.inv_bias : kInvOne);
+        if (alive & (1u << w)) u[w] = a.indices[row + 4u * gl + w];
+      bool any_c = false, any_u = false;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (alive & (1u << w)) {
+          cached[w] = is_cached(a, (int64_t)u[w]);
+          any_c |= cached[w];
+          any_u |= !cached[w];
+        }
+      }
+      // keys are needed only when the group's neighbourhood mixes both classes (otherwise K is
+      // monotone in x and the order is "larger draw first")
+      const uint64_t mc = __ballot(any_c), mu = __ballot(any_u);
+      mixed = (mc & group_lanes) != 0 && (mu & group_lanes) != 0;
     }
-  }
-  uint32_t chosen = 0;
-  for (uint32_t it = 0; it < m; ++it) {
-    // lane-local best remaining slot under (K ascending, x descending, word ascending)
-    int bw = -1;
-    uint64_t bK = ~0ull;
-    uint32_t bx = 0;
+    uint32_t own[4];  // ascending is better; ~0 for no slot (a slot that drew 0 ranks with those)
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const bool better = (alive & (1u << w)) && (bw < 0 || K[w] < bK || (K[w] == bK && x[w] > bx));
-      if (better) {
-        bw = w;
-        bK = K[w];
-        bx = x[w];
+      own[w] = ~0u;
+      if (alive & (1u << w)) {
+        own[w] = ~x[w];
+        if (kMode != kUniform && mixed)  // K < 2^38: its upper 32 bits
+          own[w] = (uint32_t)(sample_key(x[w], cached[w] ? a.bias_q16 : 65536u, cached[w] ? a.inv_bias : kInvOne) >> 6);
       }
     }
-    // group-wide best: smallest K, then largest x, then lowest lane (= lowest slot)
-    uint64_t gK = bK;
+#pragma unroll 1
+    for (uint32_t it = 0; it < m; ++it) {
+      const uint32_t best = group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3])));
 #pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) {
-      const uint64_t other = __shfl_xor(gK, o, G);
-      gK = other < gK ? other : gK;
+      for (int w = 0; w < 4; ++w) own[w] = own[w] == best ? ~0u : own[w];
     }
-    const bool tiedK = bw >= 0 && bK == gK;
-    uint32_t gx = tiedK ? bx : 0u;
+    uint32_t in_rounds = 0, n_chosen = 0;
 #pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) {
-      const uint32_t other = __shfl_xor(gx, o, G);
-      gx = other > gx ? other : gx;
+    for (int w = 0; w < 4; ++w) {
+      in_rounds |= own[w] == ~0u ? (1u << w) : 0u;
+      in_rounds &= alive;
+      n_chosen += (uint32_t)__popcll(__ballot((in_rounds >> w) & 1u) & group_lanes);
     }
-    const bool top = tiedK && bx == gx;
-    const uint32_t tops = (uint32_t)((__ballot(top) >> gshift) & ((1ull << G) - 1ull));
-    const uint32_t winner = (uint32_t)__ffs((int)tops) - 1u;
-    if (gl == winner) {
-      alive &= ~(1u << bw);
-      chosen |= 1u << bw;
+    if (draw) chosen = in_rounds;
+    const bool tie = draw && n_chosen != m;
+    if (__ballot(tie)) {
+      uint64_t K[4] = {0, 0, 0, 0};
+      uint32_t rest = alive, picked = 0;
+      if (kMode != kUniform && mixed) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          if (alive & (1u << w))
+            K[w] = sample_key(x[w], cached[w] ? a.bias_q16 : 65536u, cached[w] ? a.inv_bias : kInvOne);
+      }
+#pragma unroll 1
+      for (uint32_t it = 0; it < m; ++it) {
+        // lane-local best remaining slot under (K ascending, x descending, word ascending)
+        uint32_t best = 0, bx = 0;
+        uint64_t bK = ~0ull;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          if ((rest & (1u << w)) && (best == 0 || K[w] < bK || (K[w] == bK && x[w] > bx))) {
+            best = 1u << w;
+            bK = K[w];
+            bx = x[w];
+          }
+        }
+        // group-wide best: smallest K, then largest x, then lowest lane (= lowest slot)
+        const uint64_t gK = group_min_u64<G>(bK);
+        const bool tied_K = best != 0 && bK == gK;
+        const uint32_t gx = group_max_u32<G>(tied_K ? bx : 0u);
+        const bool mine = tied_K && bx == gx;
+        if (mine && (__ballot(mine) & lower_lanes) == 0) {
+          rest &= ~best;
+          picked |= best;
+        }
+      }
+      if (tie) chosen = picked;
     }
+    wave_sync();
+  } else {
+    put_pending<IdxT>(a, n_dst, pending);
   }
-  // emit in slot order: slots of lower lanes first, then lower words of the own lane
-  uint32_t below = 0;
-  uint32_t own_before[4];
-  uint32_t acc = 0;
+  // the chosen slots in slot order: those of lower lanes first, then lower words of the own lane
+  uint32_t at = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const uint32_t bits = (uint32_t)((__ballot((chosen >> w) & 1u) >> gshift) & ((1ull << G) - 1ull));
-    below += (uint32_t)__popc(bits & ((1u << gl) - 1u));
-    own_before[w] = acc;
-    acc += (chosen >> w) & 1u;
-  }
+  for (int w = 0; w < 4; ++w) at += (uint32_t)__popcll(__ballot((chosen >> w) & 1u) & lower_lanes);
 #pragma unroll
   for (int w = 0; w < 4; ++w)
-    if ((chosen >> w) & 1u) emit(below + own_before[w], 4u * gl + w);
+    if ((chosen >> w) & 1u) keys[at++] = 4u * gl + w;
+  wave_sync();
+  put_list<IdxT, G>(a, row, base, n_dst, min(deg, m), keys, nullptr, pending);
+  wave_sync();  // the list is rewritten by the wavefront's next nodes
+}
+
+// ---- sixteen lanes, one node of 33 to kGroupDegree neighbours -----------------------------------
+// Four nodes per wavefront.  A step draws 64 slots of each; slots whose draw clears the threshold go
+// to the group's list in LDS, in slot order, as 32-bit keys (~draw: ascending is better) beside
+// their slots.  With at most kListCap candidates a lane holds up to four of them in registers; the m
+// smallest are taken out in m rounds of a minimum over the sixteen lanes (9 to 15 instructions a
+// round for four nodes).  A chosen candidate's output position is a scan of the chosen ones before it.
+// Equal keys leave more than m chosen (weighted: keys that agree in their upper 32 bits): such a
+// node, and one whose list came out too short or too long, is left to the wavefront path (false).
+// Weighted: the list decides as in weighted_from_first_list (at least m of it cached), or if it holds
+// the whole neighbourhood; rows of up to 64 get a second attempt with exactly that.
+// Where rows are short a node's fixed costs are what counts, and memory round trips: a wavefront per
+// node spent some 350 vector instructions on a row of 65 to 512 neighbours and waited four fifths of its
+// time.  Third hop of 616 k nodes (190 k of them above 64 neighbours), fanout 5: 303 -> 196 us, 98.7 M ->
+// 65 M vector instructions; 337 k nodes on 100 M: 396 -> 269 us; 237 k nodes weighted: 262 -> 177 us.
+constexpr uint32_t kListCap = 64;
+constexpr uint32_t kListStride = kListCap + 4;  // one entry takes what does not fit; groups start in other banks
+constexpr uint32_t kGroupLdsEntries = 4 * kListStride;  // uint64 entries per wavefront: keys, slots of four groups
+
+// leaves the chosen slots in keys [m] (and, where the ids had to be looked up, the ids in slots)
+template <typename IdxT, int kMode, int NK>
+__device__ __forceinline__ bool finish_list(const SampleArgs<IdxT>& a, int64_t row, uint32_t deg, uint32_t m,
+                                            uint32_t* keys, uint32_t* slots, uint32_t cnt, bool good, bool both_classes) {
+  const uint32_t gl = local_lane_id() & 15u;
+  uint32_t own[NK], slot[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    const uint32_t at = (uint32_t)k * 16u + gl;
+    own[k] = ~0u;
+    if (good && at < cnt) own[k] = keys[at];  // below ~0: the threshold is at least 1
+    slot[k] = slots[at];
+  }
+  bool decided = good;
+  IdxT u[NK];
+  if (kMode != kUniform && both_classes) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+      if (own[k] != ~0u) u[k] = a.indices[row + slot[k]];
+    bool cached[NK];
+    uint32_t n_c = 0;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      cached[k] = own[k] != ~0u && is_cached(a, (int64_t)u[k]);
+      n_c += cached[k] ? 1u : 0u;
+    }
+    n_c = row16_last(row16_incl_scan(n_c));
+    decided = good && (n_c >= m || cnt == deg);
+    const bool mixed = decided && n_c != 0 && n_c != cnt;  // else the keys are monotone in the draws
+    if (__ballot(mixed)) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        if (mixed && own[k] != ~0u) {
+          // K < 2^38: its upper 32 bits
+          own[k] = (uint32_t)(sample_key(~own[k], cached[k] ? a.bias_q16 : 65536u, cached[k] ? a.inv_bias : kInvOne) >> 6);
+        }
+      }
+    }
+  }
+#pragma unroll 1
+  for (uint32_t it = 0; it < m; ++it) {
+    uint32_t best = own[0];
+#pragma unroll
+    for (int k = 1; k < NK; ++k) best = min(best, own[k]);
+    best = group_min_u32<16>(best);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) own[k] = own[k] == best ? ~0u : own[k];
+  }
+  uint32_t mine = 0;  // a byte per k: the lane's candidate is chosen
+#pragma unroll
+  for (int k = 0; k < NK; ++k)
+    mine |= (good && (uint32_t)k * 16u + gl < cnt && own[k] == ~0u) ? 1u << (8 * k) : 0u;
+  const uint32_t incl = row16_incl_scan(mine);
+  const uint32_t total = row16_last(incl);
+  const bool done = decided && (total * 0x01010101u) >> 24 == m;  // the sum of the bytes
+  const uint32_t pos = incl - mine + total * 0x01010100u;         // byte k: chosen ones before the lane's
+  wave_sync();
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    if (done && ((mine >> (8 * k)) & 1u)) {
+      const uint32_t at = (pos >> (8 * k)) & 255u;
+      keys[at] = slot[k];
+      if (kMode != kUniform && both_classes && m <= kListIds) {
+        slots[at] = (uint32_t)(uint64_t)(int64_t)u[k];
+        if (sizeof(IdxT) == 8) slots[kListIds + at] = (uint32_t)((uint64_t)(int64_t)u[k] >> 32);
+      }
+    }
+  }
+  return done;
+}
+
+template <typename IdxT, int kMode>
+__device__ __forceinline__ bool sample_node_16(const SampleArgs<IdxT>& a, const int32_t* tile_offs, const NodeRec& r,
+                                               bool live, int32_t n_dst, uint32_t* lds, bool both_classes,
+                                               PendingEdge<IdxT>& pending) {
+  const uint32_t lane = local_lane_id();
+  const uint32_t gl = lane & 15u;
+  uint32_t* keys = lds + (lane >> 4) * 2 * kListStride;
+  uint32_t* slots = keys + kListStride;
+  const uint32_t deg = live ? r.deg : 0;
+  const uint32_t m = (uint32_t)a.fanout;
+  const int32_t base = live ? tile_offs[r.i >> kTileShift] + r.local_off : 0;
+  if (live && gl == 0) a.blk_indptr[r.i] = base;
+  const bool whole = deg <= m;  // every neighbour is kept
+  bool open = !whole;
+  bool failed = false;
+  const PhiloxKey pk{(uint32_t)(uint64_t)r.v, (uint32_t)((uint64_t)r.v >> 32), (uint32_t)a.hop, a.seed_lo, a.seed_hi};
+  for (int attempt = 0;; ++attempt) {
+    // at least 1: out-of-range slots take part as draws of 0 (and a slot that really drew 0 is the
+    // worst of more than m)
+    uint32_t X0 = 1;
+    if (attempt == 0 && deg > a.group_lambda)
+      X0 = 0u - (uint32_t)(__fdividef((float)a.group_lambda, (float)deg) * 4294967296.0f);
+    const uint32_t n_slots = open ? deg : 0;
+    uint32_t cnt = 0;  // same value in the lanes of a group
+#pragma unroll 1
+    for (uint32_t q = gl; __ballot(4u * q < n_slots) != 0; q += 16) {
+      uint32_t x[4];
+      philox4x32_10(q, pk, x);
+      const int32_t left = (int32_t)n_slots - (int32_t)(4u * q);
+      bool pass[4];
+      uint32_t n = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        x[w] = left > w ? x[w] : 0u;
+        pass[w] = x[w] >= X0;
+        n += pass[w] ? 1u : 0u;
+      }
+      const uint32_t incl = row16_incl_scan(n);
+      uint32_t at = cnt + incl - n;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (pass[w]) {
+          const uint32_t to = min(at, kListCap);
+          keys[to] = ~x[w];
+          slots[to] = 4u * q + (uint32_t)w;
+          ++at;
+        }
+      }
+      cnt += row16_last(incl);
+    }
+    if (attempt == 0) put_pending<IdxT>(a, n_dst, pending);  // of the wavefront's previous nodes
+    wave_sync();
+    const bool good = open && cnt >= m && cnt <= kListCap;
+    const uint32_t listed = good ? cnt : 0u;
+    uint32_t max_cnt = 0;  // of the wavefront's four lists
+#pragma unroll
+    for (int g = 0; g < 4; ++g) max_cnt = max(max_cnt, (uint32_t)__builtin_amdgcn_readlane((int32_t)listed, 16 * g));
+    bool done = false;
+    if (max_cnt > 32)
+      done = finish_list<IdxT, kMode, 4>(a, r.row, deg, m, keys, slots, cnt, good, both_classes);
+    else if (max_cnt > 0)
+      done = finish_list<IdxT, kMode, 2>(a, r.row, deg, m, keys, slots, cnt, good, both_classes);
+    if (attempt == 0 && whole)
+      for (uint32_t s = gl; s < deg; s += 16) keys[s] = s;
+    wave_sync();
+    const bool ids_known = kMode != kUniform && both_classes && m <= kListIds && __ballot(whole && live) == 0;
+    const uint32_t k = done ? m : attempt == 0 && whole ? deg : 0u;
+    if (__ballot(k != 0) != 0)
+      put_list<IdxT, 16>(a, r.row, base, n_dst, k, keys, ids_known ? slots : nullptr, pending);
+    wave_sync();  // the lists are rewritten
+    open = open && !done;
+    if (kMode == kUniform || attempt != 0) break;
+    failed = open && deg > kListCap;
+    open = open && !failed;
+    if (__ballot(open) == 0) break;
+    put_pending<IdxT>(a, n_dst, pending);  // the second attempt has edges of its own
+  }
+  return !(open || failed);
 }
 
 // ---- a workgroup, one hub ---------------------------------------------------------------------
@@ -902,7 +1235,7 @@ template <typename IdxT, int kMode>
 __device__ __forceinline__ void hub_scan(const SampleArgs<IdxT>& a, const NodeRec& r, uint64_t* lds,
                                          uint64_t*& joined_out, uint64_t*& rest_out, uint32_t& pre_cnt,
                                          uint32_t& pre_cnt_b, bool both_classes) {
-  const uint32_t lane = lane_id();
+  const uint32_t lane = local_lane_id();
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
   const uint32_t n_waves = blockDim.x >> 6;
   uint64_t* region = lds + (size_t)wave * kHubRegion;         // [kHubRegion]
@@ -1014,86 +1347,92 @@ __device__ __forceinline__ void hub_scan(const SampleArgs<IdxT>& a, const NodeRe
   pre_cnt_b = want_b ? *shared_cnt_b : 0u;
 }
 
-template <typename IdxT, int G, int kMode>
-__device__ __forceinline__ void run_group_role(const SampleArgs<IdxT>& a, const int32_t* tile_offs,
-                                               int bin, uint32_t block_in_role,
-                                               uint32_t blocks_in_role, int32_t n_dst, bool both_classes) {
-  const int64_t count = a.st->bin_count[bin];
-  const uint32_t per_block = blockDim.x / G;
-  const int64_t groups = (int64_t)blocks_in_role * per_block;
-  int64_t item = (int64_t)block_in_role * per_block + threadIdx.x / G;
-  NodeRec cur = {};
-  if (item < count) cur = a.bins[bin][item];
-  for (; item < count; item += groups) {
-    NodeRec nxt = {};
-    if (item + groups < count) nxt = a.bins[bin][item + groups];  // in flight while cur is sampled
-    if (cur.i >= 0 && cur.i < n_dst) sample_node_group<IdxT, G, kMode>(a, tile_offs, cur, n_dst, both_classes);
-    cur = nxt;
-  }
-}
-
 constexpr int kSampleMaxThreads = 256;
 
-// Workgroups take roles by index: the first role_blocks[4] serve the hubs (one workgroup each), the
-// next role_blocks[3] the wide nodes (one wavefront each), then role_blocks[2], [1], [0] the
-// small-degree bins with lane groups of 16, 8, 4.
+// Workgroups take roles by index: hub_blocks serve the hubs (one workgroup each), wide_blocks the wide
+// nodes (one wavefront each), group_blocks the nodes of bins 0-7 (a wavefront takes 4, 8 or 16
+// nodes of one bin at a time).
 template <typename IdxT, int kMode>
-__global__ __launch_bounds__(kSampleMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_sample(const SampleArgs<IdxT> a) {
+__global__ __launch_bounds__(kSampleMaxThreads) __attribute__((amdgpu_waves_per_eu(kMode == kUniform ? 5 : 4))) void k_sample(const SampleArgs<IdxT> a) {
   extern __shared__ uint64_t lds[];
   __shared__ int32_t fused_offs[kFuseTiles];
   __shared__ uint32_t fused_total;
   __shared__ uint32_t block_left;
-  // Workgroups start in index order, so the roles with the longest-running workgroups come
-  // first (hubs, then wide nodes) and the short ones of the small-degree bins fill the end of the
-  // launch; the other way round the hubs would start last and the launch end with their tail.
+  // Workgroups start in index order, so the roles whose workgroups run longest come first (hubs, then
+  // the lane groups, which have a dozen nodes' chains each) and the single wide nodes fill the end
+  // of the launch (wide nodes before the groups: hop 3 of a mini-batch 214 instead of 199 us at 616 k
+  // nodes, 294 instead of 289 at 337 k).
   uint32_t b = blockIdx.x;
-  const bool hub_role = b < a.role_blocks[4];  // the same for the whole workgroup
-  int group_bin = -1;
+  const bool hub_role = b < a.hub_blocks;  // the same for the whole workgroup
+  bool group_role = false;
   if (!hub_role) {
-    b -= a.role_blocks[4];
-    if (b >= a.role_blocks[3]) {
-      b -= a.role_blocks[3];
-      group_bin = 2;
-      if (b >= a.role_blocks[2]) {
-        b -= a.role_blocks[2];
-        group_bin = 1;
-        if (b >= a.role_blocks[1]) {
-          b -= a.role_blocks[1];
-          group_bin = 0;
-        }
-      }
-    }
+    b -= a.hub_blocks;
+    group_role = b < a.group_blocks;
+    if (!group_role) b -= a.group_blocks;
   }
   // the wavefront's index inside the workgroup, held in a scalar register so that the node loops
   // below are uniform control flow for the whole wavefront
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
   const uint32_t n_waves = blockDim.x >> 6;
   const uint32_t lane = lane_id();
-  // wide nodes and hubs share one loop (and one copy of the selection code): a wavefront takes a
-  // wide node by itself; a hub is scanned by the whole workgroup and finished by wavefront 0
-  const int bin = hub_role ? 4 : 3;
-  NodeRec* recs = a.bins[bin];
-  const int64_t stride = hub_role ? (int64_t)a.role_blocks[4] : (int64_t)a.role_blocks[3] * n_waves;
+  uint32_t count[kNumBins];
+#pragma unroll
+  for (int k = 0; k < kNumBins; ++k) count[k] = (uint32_t)a.bin_count[k * kBinCountStride];
+  const int64_t stride = hub_role ? (int64_t)a.hub_blocks
+                                  : (int64_t)(group_role ? a.group_blocks : a.wide_blocks) * n_waves;
   const int64_t first = hub_role ? (int64_t)b : (int64_t)b * n_waves + wave;
-  int64_t n_nodes = 0;
-  // kWeightedFull walks its list 64 records at a time, one per lane: as a second launch it takes
-  // only the marked ones, and most workgroups find none and leave here, before anything else
+  // Where item t of the role's list is.  Wide nodes and hubs: record t of the bin; as a second launch
+  // the wide role goes through the records of the lane groups' bins too (those that hold marks).
+  uint32_t n_items = hub_role ? count[kHubBin] : count[kWideBin];
+  if (kMode == kWeightedFull && a.left_only && !hub_role) {
+#pragma unroll
+    for (int k = kWideBin - 1; k >= 3; --k) n_items += count[k];
+    if (a.st->left_small) n_items += count[2];
+  }
+  auto wide_rec = [&](int64_t t) {
+    if (hub_role) return bin_rec(a.bins, kHubBin, t);
+    int bin = kWideBin;
+    if (kMode == kWeightedFull) {
+#pragma unroll
+      for (int k = kWideBin; k > 2; --k)
+        if (bin == k && t >= (int64_t)count[k]) {
+          t -= (int64_t)count[k];
+          bin = k - 1;
+        }
+    }
+    return bin_rec(a.bins, bin, t);
+  };
+  // kWeightedFull as a second launch takes only the marked records, and most workgroups find none
+  // and leave here, before anything else
   uint64_t round0 = 0;
   uint32_t n_left = 0;
   if constexpr (kMode == kWeightedFull) {
-    if (group_bin < 0) {
-      n_nodes = a.st->bin_count[bin];
-      const int64_t tl = first + (int64_t)lane * stride;
-      round0 = __ballot(tl < n_nodes && (!a.left_only || recs[tl].left != 0));
-    }
     if (a.left_only) {
+      const int64_t tl = first + (int64_t)lane * stride;
+      round0 = __ballot(tl < n_items && wide_rec(tl)->left != 0);
       if (threadIdx.x == 0) block_left = 0;
-      if (!__syncthreads_or(round0 != 0 || first + 64 * stride < n_nodes)) return;
+      if (!__syncthreads_or(round0 != 0 || first + 64 * stride < n_items)) return;
     }
   }
   const int32_t* tile_offs = a.tile_offs;
   TileSums sums = {};
   if (tile_offs == nullptr) sums = tile_sums_load(a.tile_sums, a.cap_tiles);  // does not wait for n_dst
+  // items of the lane groups: wavefront loads of one bin, the longest rows first
+  uint32_t end_of[kWideBin];  // items up to and including bin k
+  if (group_role) {
+    uint32_t run = 0;
+#pragma unroll
+    for (int k = kWideBin - 1; k >= 0; --k) {
+      const uint32_t per_wave = k >= 2 ? 4 : k == 1 ? 8 : 16;
+      run += (count[k] + per_wave - 1) / per_wave;
+      end_of[k] = run;
+    }
+    n_items = run;
+  }
+  // A workgroup without work leaves once the counts are there, which it waits for no longer than for
+  // the tile sums: thousands of them are surplus (the launch is sized for bounds), and their scans of
+  // the tile sums held the others up.  Workgroup 0 stays, it publishes the hop's edge count.
+  if (blockIdx.x != 0 && (hub_role ? (int64_t)b : (int64_t)b * n_waves) >= (int64_t)n_items) return;
   const int32_t n_dst = a.st->n_dst[a.hop];
   const bool both_classes = kMode != kUniform && a.st->class_mix == 3;  // read once, not per node
   if (tile_offs == nullptr) {  // few tiles: scan the tile sums here, publish the hop's edge count
@@ -1105,55 +1444,86 @@ __global__ __launch_bounds__(kSampleMaxThreads) __attribute__((amdgpu_waves_per_
       a.blk_indptr[n_dst] = (int32_t)total;
     }
   }
-  if (group_bin == 2) return run_group_role<IdxT, 16, kMode>(a, tile_offs, 2, b, a.role_blocks[2], n_dst, both_classes);
-  if (group_bin == 1) return run_group_role<IdxT, 8, kMode>(a, tile_offs, 1, b, a.role_blocks[1], n_dst, both_classes);
-  if (group_bin == 0) return run_group_role<IdxT, 4, kMode>(a, tile_offs, 0, b, a.role_blocks[0], n_dst, both_classes);
   uint64_t* my_lds = lds + (size_t)wave * a.lds_per_wave;
-  auto sample_one = [&](const NodeRec& cur, int32_t* left) {
-    if (cur.i >= 0 && cur.i < n_dst) {
+  // Every role ends in the same loop, so that the selection of one wavefront for one node exists once
+  // in the kernel: `cur` holds a record per lane, `todo` says whose are to be sampled.
+  PendingEdge<IdxT> pending = {};
+  // item t of the lane groups: its bin, the lane's record (null: none)
+  auto group_rec = [&](int64_t t, int& bin) -> NodeRec* {
+    bin = kWideBin - 1;
+    uint32_t begin = 0;
+#pragma unroll
+    for (int k = kWideBin - 1; k > 0; --k)
+      if (t >= (int64_t)end_of[k]) {
+        bin = k - 1;
+        begin = end_of[k];
+      }
+    const uint32_t in_bin = (uint32_t)a.bin_count[bin * kBinCountStride];
+    const uint32_t shift = bin >= 2 ? 4 : bin == 1 ? 3 : 2;  // log2 of the lanes per node
+    const uint32_t pos = (((uint32_t)t - begin) << (6 - shift)) + (lane >> shift);
+    return t < (int64_t)n_items && pos < in_bin ? bin_rec(a.bins, bin, pos) : nullptr;
+  };
+  int bin_ahead = 0;
+  NodeRec* where_ahead = nullptr;
+  NodeRec ahead = {};
+  if (group_role) {
+    where_ahead = group_rec(first, bin_ahead);
+    if (where_ahead) ahead = *where_ahead;
+  }
+  for (int64_t t0 = first; t0 < (int64_t)n_items; t0 += group_role ? stride : 64 * stride) {
+    NodeRec cur = {};
+    NodeRec* where = nullptr;  // of cur, where marks are left
+    uint64_t todo = 0;
+    if (group_role) {
+      cur = ahead;
+      where = where_ahead;
+      const int bin = bin_ahead;
+      const bool live = where && cur.i >= 0 && cur.i < n_dst;
+      where_ahead = group_rec(t0 + stride, bin_ahead);  // in flight while cur is sampled
+      if (where_ahead) ahead = *where_ahead;
+      if (bin >= 2) {
+        const bool ok = sample_node_16<IdxT, kMode>(a, tile_offs, cur, live, n_dst, (uint32_t*)my_lds, both_classes, pending);
+        todo = __ballot(!ok) & 0x0001000100010001ull;  // one lane of each group
+        if (kMode == kWeightedFast && bin == 2 && todo != 0 && lane == 0) atomicOr(&a.st->left_small, 1);
+      } else if (bin == 1) {
+        sample_node_group<IdxT, 8, kMode>(a, tile_offs, cur, live, n_dst, (uint32_t*)my_lds, both_classes, pending);
+      } else {
+        sample_node_group<IdxT, 4, kMode>(a, tile_offs, cur, live, n_dst, (uint32_t*)my_lds, both_classes, pending);
+      }
+    } else {
+      const int64_t tl = t0 + (int64_t)lane * stride;
+      bool take = tl < (int64_t)n_items;
+      if (take) where = wide_rec(tl);
+      if (kMode == kWeightedFull && a.left_only) take = t0 == first ? (round0 >> lane) & 1u : take && where->left != 0;
+      if (take) {
+        cur = *where;
+        take = cur.i >= 0 && cur.i < n_dst;
+      }
+      todo = __ballot(take);
+      n_left += (uint32_t)__popcll(todo);
+    }
+    while (todo) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+      todo &= todo - 1;
+      const NodeRec one = readlane_rec(cur, l);
+      int32_t* left = nullptr;
+      if (kMode == kWeightedFast) left = &reinterpret_cast<NodeRec*>(readlane_u64((uint64_t)(uintptr_t)where, l))->left;
       uint64_t* cand = my_lds;
       uint64_t* rest = my_lds + a.cap;
       uint32_t pre_cnt = 0, pre_cnt_b = 0;
-      if (hub_role) hub_scan<IdxT, kMode>(a, cur, lds, cand, rest, pre_cnt, pre_cnt_b, both_classes);
+      if (hub_role) hub_scan<IdxT, kMode>(a, one, lds, cand, rest, pre_cnt, pre_cnt_b, both_classes);
       if (!hub_role || wave == 0)
-        sample_node_wave<IdxT, kMode>(a, tile_offs, cur, n_dst, cand, rest, hub_role, pre_cnt, pre_cnt_b,
+        sample_node_wave<IdxT, kMode>(a, tile_offs, one, n_dst, cand, rest, hub_role, pre_cnt, pre_cnt_b,
                                       both_classes, left);
       if (hub_role) __syncthreads();  // the regions are reused for the workgroup's next hub
     }
-  };
+  }
+  put_pending<IdxT>(a, n_dst, pending);
   if constexpr (kMode == kWeightedFull) {
-    for (int64_t t0 = first; t0 < n_nodes; t0 += 64 * stride) {
-      uint64_t todo = round0;
-      if (t0 != first) {
-        const int64_t tl = t0 + (int64_t)lane * stride;
-        todo = __ballot(tl < n_nodes && (!a.left_only || recs[tl].left != 0));
-      }
-      n_left += (uint32_t)__popcll(todo);
-      NodeRec cur = {};
-      if (todo) cur = recs[t0 + (int64_t)__builtin_ctzll(todo) * stride];
-      while (todo) {
-        todo &= todo - 1;
-        NodeRec nxt = {};
-        if (todo) nxt = recs[t0 + (int64_t)__builtin_ctzll(todo) * stride];  // in flight while cur is sampled
-        sample_one(cur, nullptr);
-        cur = nxt;
-      }
-    }
     if (a.left_only) {  // the call's count of nodes that needed this launch: one atomic per workgroup
       if (lane == 0 && n_left != 0 && (!hub_role || wave == 0)) atomicAdd(&block_left, n_left);
       __syncthreads();
       if (threadIdx.x == 0 && block_left != 0) atomicAdd(&a.st->n_deferred[hub_role ? 1 : 0], (int32_t)block_left);
-    }
-  } else {
-    n_nodes = a.st->bin_count[bin];
-    int64_t t = first;
-    NodeRec cur = {};
-    if (t < n_nodes) cur = recs[t];
-    for (; t < n_nodes; t += stride) {
-      NodeRec nxt = {};
-      if (t + stride < n_nodes) nxt = recs[t + stride];  // in flight while cur is sampled
-      sample_one(cur, &recs[t].left);
-      cur = nxt;
     }
   }
 }

@@ -45,7 +45,8 @@ struct a3_ctx {
   int32_t* tile_sums2 = nullptr;  // per edge tile: first occurrences
   int32_t* tile_offs = nullptr;   // edge offsets of the node tiles (read by k_sample)
   int32_t* tile_offs2 = nullptr;  // new-node offsets of the edge tiles (read by k_relabel)
-  a3::NodeRec* bins[a3::kNumBins] = {nullptr};  // frontier node records by degree bin
+  a3::NodeRec* bin_arrays[a3::kBinArrays] = {nullptr};  // frontier node records by degree bin
+  int32_t* bin_count = nullptr;
   int32_t* node_map = nullptr;  // global id -> map_base + position, grown on demand
   int64_t node_map_cap = 0;
   int64_t map_floor = 0;        // the lowest value any call has written into node_map so far
@@ -167,11 +168,51 @@ uint32_t challenger_cap(int32_t fanout, uint32_t capb) {
   return std::max<uint32_t>(64u, (both + 1u) / 2u);
 }
 
-// uint64 entries of LDS one wavefront needs in the wavefront-per-node path
+// The 16-lane groups keep a list of kListCap = 64 candidates per node.  Fewer than m or more than 64
+// send a node to the wavefront path, which costs about ten times a group's share: rarer than one in a
+// thousand up to fanout 20, one in a hundred at 32 (weighted lists are longer, for enough of them
+// has to be cached).
+// They serve frontiers that fill the chip with a quarter of a wavefront per node.  In smaller ones a
+// wavefront per node has the shorter chain: hop 0 of 1 024 nodes with fanout 25 takes 11.8 us with
+// wavefronts and 15.5 with groups, of 4 096 (weighted) 20.1 and 23.2; hop 1 of some 20 k nodes
+// (bound 26 k) 52.7 and 44.6.
+// Hubs, rows that a workgroup scans together, begin at kHubDegreeMany / Few: three of its four
+// wavefronts wait while one selects, which a full chip feels (337 k nodes, 15.7 k of them between
+// 4 096 and 16 384: 277 us from 4 096 on, 269 from 8 192, 269 from 16 384; 20 k nodes of a dense
+// graph 44.9, 44.6, 47.7), and an idle one does not (hop 0 of 1 024 nodes 11.8 from 4 096, 13.9 from 8 192).
+constexpr int64_t kGroupNodes = 8192;
+constexpr uint32_t kHubDegreeMany = 8192, kHubDegreeFew = 4096;
+constexpr int32_t kGroupFanout = 32;
+constexpr int32_t kGroupWeightedFanout = 16;
+uint32_t group_lambda_for(int32_t m, bool weighted) {
+  const double want = weighted ? m + 5.0 * std::sqrt((double)m) + 9.0 : m + 3.0 * std::sqrt((double)m) + 5.0;
+  return (uint32_t)std::min(want, 45.0);
+}
+
+// uint64 entries of LDS one wavefront needs in the wavefront-per-node path and for its groups' lists
 uint32_t sample_lds_entries(uint32_t cap, int32_t fanout, bool weighted, uint32_t capb) {
   uint32_t entries = cap + (uint32_t)fanout;
   if (weighted) entries += 3 * (uint32_t)fanout + 2 * challenger_cap(fanout, capb) + capb;
-  return entries;
+  return (std::max<uint32_t>(entries, a3::kGroupLdsEntries) + 1u) & ~1u;  // the lists are read 16 bytes at a time
+}
+
+// the first record of a bin (see a3::bin_rec)
+a3::NodeRec* first_record(const a3_ctx* ctx, int bin) {
+  if (bin < a3::kBinArrays) return ctx->bin_arrays[bin];
+  return ctx->bin_arrays[bin - a3::kBinArrays] + std::max<int64_t>(ctx->cap_dst[ctx->max_hops - 1], 1) - 1;
+}
+
+// workgroups per role of k_sample: enough to cover a frontier of nb nodes once, at most
+// kMaxRoleWaves wavefronts
+template <typename Args>
+void set_roles(const a3_ctx* ctx, Args& sa, int64_t nb, int n_waves) {
+  const int64_t max_blocks = std::max<int64_t>(kMaxRoleWaves / n_waves, 1);
+  const int64_t group_items = (nb + 3) / 4 + a3::kWideBin;  // every bin may end in a part of an item
+  sa.hub_blocks = (uint32_t)std::min<int64_t>(nb, kMaxHubBlocks);
+  sa.wide_blocks = (uint32_t)std::min<int64_t>((nb + n_waves - 1) / n_waves, max_blocks);
+  sa.group_blocks = (uint32_t)std::min<int64_t>((group_items + n_waves - 1) / n_waves, max_blocks);
+  if (ctx->flags & A3_TEST_SMALL_GRID)
+    for (uint32_t* rb : {&sa.hub_blocks, &sa.wide_blocks, &sa.group_blocks}) *rb = std::min(*rb, 2u);
 }
 
 // A3_PROFILE brackets every kind of call, A3_PROFILE_RETRIEVE the retrieves (kind 1) only: an
@@ -409,7 +450,12 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
     fa.fanout = f;
     fa.tile_sums = ctx->tile_sums;
     fa.num_nodes = num_nodes;
-    for (int b = 0; b < a3::kNumBins; ++b) fa.bins[b] = ctx->bins[b];
+    for (int b = 0; b < a3::kNumBins; ++b) fa.bins[b] = first_record(ctx, b);
+    fa.bin_count = ctx->bin_count;
+    const bool groups = !full_only && !(ctx->flags & A3_FORCE_RADIX) && bound_dst[h] > kGroupNodes &&
+                        f <= (weighted ? kGroupWeightedFanout : kGroupFanout);
+    fa.groups = groups ? 1 : 0;
+    fa.hub_degree = groups ? kHubDegreeMany : kHubDegreeFew;
     hipLaunchKernelGGL(a3::k_frontier<IdxT>, dim3(dst_tiles), dim3(a3::kTileThreads), 0, st, fa);
     // few tiles: the consumer scans the tile sums itself and the launch is saved
     const bool fuse_dst = dst_tiles <= (unsigned)a3::kFuseTiles;
@@ -433,7 +479,8 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
       sa.node_map = ctx->node_map;
       sa.map_base = ctx->map_base;
       sa.st = ds;
-      for (int b = 0; b < a3::kNumBins; ++b) sa.bins[b] = ctx->bins[b];
+      for (int b = 0; b < a3::kNumBins; ++b) sa.bins[b] = first_record(ctx, b);
+      sa.bin_count = ctx->bin_count;
       sa.num_nodes = num_nodes;
       sa.cap_edges = ctx->cap_edges[h];
       sa.left_only = 0;
@@ -442,7 +489,12 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
       const bool few_draws = (ctx->flags & A3_TEST_FEW_DRAWS) != 0;
       sa.lambda = weighted ? lambda_for_first_list(f) : lambda_for(f);
       sa.cap = cap_for(sa.lambda);
-      if (few_draws) sa.lambda = std::max<uint32_t>(1u, (uint32_t)f / 2u);
+      // where the groups serve only rows that fit their lists, the lists take the whole rows
+      sa.group_lambda = groups ? group_lambda_for(f, weighted) : a3::kListCap;
+      if (few_draws) {
+        sa.lambda = std::max<uint32_t>(1u, (uint32_t)f / 2u);
+        sa.group_lambda = sa.lambda;
+      }
       sa.bias_q16 = bias_q16;
       sa.inv_bias = 1.0 / (double)bias_q16;
       sa.seed_lo = (uint32_t)rng_seed;
@@ -460,18 +512,9 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
         // wavefronts per workgroup: as many as the LDS allows, at most kSampleWaves
         int n_waves = kSampleWaves;
         while (n_waves > 1 && sample_block_lds_bytes(sa.lds_per_wave, sa.cap, n_waves) > kLdsLimit) n_waves >>= 1;
-        // workgroups per role: enough to cover the frontier bound once, at most kMaxRoleWaves wavefronts
-        const int64_t max_blocks = std::max<int64_t>(kMaxRoleWaves / n_waves, 1);
         const int64_t threads = 64 * n_waves;
-        sa.role_blocks[0] = (uint32_t)std::min<int64_t>((nb * 4 + threads - 1) / threads, max_blocks);
-        sa.role_blocks[1] = (uint32_t)std::min<int64_t>((nb * 8 + threads - 1) / threads, max_blocks);
-        sa.role_blocks[2] = (uint32_t)std::min<int64_t>((nb * 16 + threads - 1) / threads, max_blocks);
-        sa.role_blocks[3] = (uint32_t)std::min<int64_t>((nb + n_waves - 1) / n_waves, max_blocks);
-        sa.role_blocks[4] = (uint32_t)std::min<int64_t>(nb, kMaxHubBlocks);
-        if (ctx->flags & A3_TEST_SMALL_GRID)
-          for (uint32_t& rb : sa.role_blocks) rb = std::min(rb, 2u);
-        const unsigned grid = sa.role_blocks[0] + sa.role_blocks[1] + sa.role_blocks[2] +
-                              sa.role_blocks[3] + sa.role_blocks[4];
+        set_roles(ctx, sa, nb, n_waves);
+        const unsigned grid = sa.hub_blocks + sa.wide_blocks + sa.group_blocks;
         const size_t lds_bytes = sample_block_lds_bytes(sa.lds_per_wave, sa.cap, n_waves);
         if (weighted)
           hipLaunchKernelGGL((a3::k_sample<IdxT, a3::kWeightedFast>), dim3(grid), dim3((unsigned)threads), lds_bytes, st, sa);
@@ -491,28 +534,17 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
         int n_waves = kSampleWaves;
         while (n_waves > 1 && sample_block_lds_bytes(sa.lds_per_wave, sa.cap, n_waves) > kLdsLimit) n_waves >>= 1;
         const int64_t threads = 64 * n_waves;
-        if (full_only) {
-          // the only launch of the hop: every node, from the frontier's own lists
-          const int64_t max_blocks = std::max<int64_t>(kMaxRoleWaves / n_waves, 1);
-          sa.role_blocks[0] = (uint32_t)std::min<int64_t>((nb * 4 + threads - 1) / threads, max_blocks);
-          sa.role_blocks[1] = (uint32_t)std::min<int64_t>((nb * 8 + threads - 1) / threads, max_blocks);
-          sa.role_blocks[2] = (uint32_t)std::min<int64_t>((nb * 16 + threads - 1) / threads, max_blocks);
-          sa.role_blocks[3] = (uint32_t)std::min<int64_t>((nb + n_waves - 1) / n_waves, max_blocks);
-          sa.role_blocks[4] = (uint32_t)std::min<int64_t>(nb, kMaxHubBlocks);
-        } else {
+        set_roles(ctx, sa, nb, n_waves);  // full_only: the only launch of the hop, every node
+        if (!full_only) {
           // A wavefront (a workgroup, for the hubs) looks at the marks of 64 records per round,
           // the records a whole launch apart: the marked ones spread over one chip's worth of
           // wavefronts however few they are.
-          const int64_t max_blocks = std::max<int64_t>(kMaxRoleWaves / n_waves / 2, 1);
           sa.left_only = 1;
-          sa.role_blocks[0] = sa.role_blocks[1] = sa.role_blocks[2] = 0;
-          sa.role_blocks[3] = (uint32_t)std::min<int64_t>((nb + n_waves - 1) / n_waves, max_blocks);
-          sa.role_blocks[4] = (uint32_t)std::min<int64_t>(nb, kMaxHubBlocks / 4);
+          sa.group_blocks = 0;
+          sa.wide_blocks = std::min(sa.wide_blocks, (uint32_t)std::max<int64_t>(kMaxRoleWaves / n_waves / 2, 1));
+          sa.hub_blocks = std::min(sa.hub_blocks, (uint32_t)(kMaxHubBlocks / 4));
         }
-        if (ctx->flags & A3_TEST_SMALL_GRID)
-          for (uint32_t& rb : sa.role_blocks) rb = std::min(rb, 2u);
-        const unsigned grid = sa.role_blocks[0] + sa.role_blocks[1] + sa.role_blocks[2] +
-                              sa.role_blocks[3] + sa.role_blocks[4];
+        const unsigned grid = sa.hub_blocks + sa.wide_blocks + sa.group_blocks;
         const size_t lds_bytes = sample_block_lds_bytes(sa.lds_per_wave, sa.cap, n_waves);
         hipLaunchKernelGGL((a3::k_sample<IdxT, a3::kWeightedFull>), dim3(grid), dim3((unsigned)threads),
                            lds_bytes, st, sa);
@@ -533,6 +565,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
     ra.tile_sums = ctx->tile_sums2;
     ra.cap_tiles = std::min<int64_t>(ctx->cap_tiles, edge_tiles);
     ra.st = ds;
+    ra.bin_count = ctx->bin_count;
     ra.hop = h;
     ra.last_hop = h == num_hops - 1 ? 1 : 0;  // nothing follows: the relabel map needs no local ids
     ra.num_nodes = num_nodes;
@@ -952,7 +985,8 @@ extern "C" int a3_create(a3_ctx** out, int hip_device, void* hip_stream, int64_t
   chk(dev_alloc(ctx, &ctx->tile_sums2, ctx->cap_tiles));
   chk(dev_alloc(ctx, &ctx->tile_offs, ctx->cap_tiles));
   chk(dev_alloc(ctx, &ctx->tile_offs2, ctx->cap_tiles));
-  for (int b = 0; b < a3::kNumBins; ++b) chk(dev_alloc(ctx, &ctx->bins[b], ctx->cap_dst[max_hops - 1]));
+  for (auto& records : ctx->bin_arrays) chk(dev_alloc(ctx, &records, ctx->cap_dst[max_hops - 1]));
+  chk(dev_alloc(ctx, &ctx->bin_count, a3::kNumBins * a3::kBinCountStride));
   chk(dev_alloc(ctx, &ctx->d_state, 1));
   chk(dev_alloc(ctx, &ctx->block_seen, kCachedBitsBlocks));
   chk(dev_alloc(ctx, &ctx->class_mix_kept, 1));
@@ -960,6 +994,8 @@ extern "C" int a3_create(a3_ctx** out, int hip_device, void* hip_stream, int64_t
     static_assert(sizeof(DevState) % sizeof(int32_t) == 0, "DevState is a block of int32");
     hipLaunchKernelGGL(a3::k_fill_i32, dim3(1), dim3(256), 0, ctx->stream, (int32_t*)ctx->d_state,
                        (int64_t)(sizeof(DevState) / sizeof(int32_t)), 0);
+    hipLaunchKernelGGL(a3::k_fill_i32, dim3(1), dim3(256), 0, ctx->stream, ctx->bin_count,
+                       (int64_t)(a3::kNumBins * a3::kBinCountStride), 0);
     e = hipGetLastError();
     if (e != hipSuccess) rc = hip_fail(ctx, e, "a3_create: clearing the state block");
   }
