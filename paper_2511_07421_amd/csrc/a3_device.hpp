@@ -36,14 +36,31 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {  // set bits of
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// exclusive prefix sum across the 64 lanes of a wave
+// A data-parallel move inside a row of 16 lanes is an operand of an ordinary vector instruction,
+// where __shfl goes through the LDS unit (some hundred cycles a step).  Lanes without a source read 0.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, kCtrl, 0xf, 0xf, true);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // i -> 7 - i in a half row, i -> 15 - i in a row
+constexpr int kDppShr = 0x110, kDppLast = 0x15F;           // lane i from i - n; every lane from lane 15
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;    // the row's / half's last lane to the next one
+
+__device__ __forceinline__ uint32_t row16_incl_scan(uint32_t v) {
+  v += dpp_u32<kDppShr + 1>(v);
+  v += dpp_u32<kDppShr + 2>(v);
+  v += dpp_u32<kDppShr + 4>(v);
+  v += dpp_u32<kDppShr + 8>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t row16_last(uint32_t v) { return dpp_u32<kDppLast>(v); }
+
+// exclusive prefix sum across the 64 lanes of a wave, all of them active
 __device__ __forceinline__ uint32_t wave_excl_scan_u32(uint32_t v) {
-  uint32_t incl = v;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t up = __shfl_up(incl, o, kWave);
-    if (lane_id() >= (uint32_t)o) incl += up;
-  }
+  uint32_t incl = row16_incl_scan(v);
+  incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)incl, kDppBcast15, 0xa, 0xf, false);  // rows 1, 3
+  incl += (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)incl, kDppBcast31, 0xc, 0xf, false);  // rows 2, 3
   return incl - v;
 }
 

@@ -16,9 +16,9 @@
 //   k_flag        which sampled edge is the first occurrence of a new node; tile-local prefix
 //   k_scan_tiles  numbering of the new nodes across tiles (as above)
 //   k_relabel     local ids of all edges, new nodes appended to the frontier with their device-map
-//                 entry (the relabel map is never cleaned: every call uses values below the last)
-// Once per call: k_cached_bits and k_class_mix (weighted calls: one bit per node from the device
-// map; which weight classes the map holds), k_publish (counts to the host).
+//                 entry (the relabel map is never cleaned: every call uses values below the last);
+//                 the last hop's launch sends the counts to the host
+// Once per call: k_cached_bits (weighted calls: one bit per node from the device map).
 // Then: k_gather (feature retrieve; k_gather_ahead where the rows of an earlier hop's nodes are
 // retrieved beside the sampling of a later hop), k_block_mean (neighbour aggregation of one block),
 // k_count_accesses / k_rank_* / k_fifo_* (cache policies), k_validate_rows / k_validate_map

@@ -74,6 +74,9 @@ __global__ __launch_bounds__(kTileThreads) void k_flag(const IdxT* gid, const in
 // Where a node is first numbered its device-map entry is looked up, once (S_slot: the retrieve
 // of the input nodes then reads its slots in sequence), and its relabel-map entry becomes its
 // local id, for the hops that follow; the last hop, which nothing follows, leaves the map alone.
+// The last hop's launch also ends the call: workgroup 0 copies the state block to the host and leaves
+// it clean for the next call, so its other workgroups report errors to the host directly (a launch
+// of its own for that took 4.2 us and the gap before it).
 constexpr int kRelabelPerThread = 4;
 
 template <typename IdxT>
@@ -87,7 +90,7 @@ struct RelabelArgs {
   DevState* st;
   int32_t* bin_count;        // the degree bins' counters, cleared for the next hop
   int32_t hop;
-  int32_t last_hop;          // this hop ends the call
+  HostState* host;           // the hop that ends the call: where the host reads the counts; else null
   int64_t num_nodes;
   int64_t cap_src;           // entries in S, S_slot
   IdxT* S;
@@ -103,6 +106,12 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
   __shared__ int32_t fused_offs[kFuseTiles];
   __shared__ uint32_t fused_total;
   const bool fuse = a.tile_offs == nullptr;
+  auto report = [&](int32_t bit) {
+    if (a.host)
+      __hip_atomic_store(&a.host->late_error, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else
+      atomicOr(&a.st->error, bit);
+  };
   TileSums sums = {};
   if (fuse) sums = tile_sums_load(a.tile_sums, a.cap_tiles);  // does not wait for the counts
   const int64_t n = a.st->n_edges[a.hop];
@@ -134,6 +143,16 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
       a.st->n_dst[a.hop + 1] = n_src;
     }
   }
+  if (a.host && blockIdx.x == 0) {
+    __syncthreads();  // thread 0's counts
+    constexpr uint32_t kWords = sizeof(DevState) / sizeof(int32_t);
+    static_assert(kWords <= (uint32_t)kTileThreads, "a thread copies a word of the state block");
+    if (threadIdx.x < kWords) {
+      int32_t* word = reinterpret_cast<int32_t*>(a.st) + threadIdx.x;
+      reinterpret_cast<int32_t*>(&a.host->st)[threadIdx.x] = *word;
+      if (threadIdx.x >= offsetof(DevState, error) / sizeof(int32_t)) *word = 0;
+    }
+  }
   // second batch of reads: the rank of every edge's first occurrence; for a first occurrence
   // itself, what is looked up of the new node
   int32_t rank_of[kRelabelPerThread], slot_of[kRelabelPerThread];
@@ -162,14 +181,14 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
     const int32_t p = p_of[k];
     int32_t local;
     if (p < 0) {
-      atomicOr(&a.st->error, kErrFirstPosNeg);
+      report(kErrFirstPosNeg);
       local = 0;
     } else if (p < n_dst) {
       local = p;
     } else {
       const int32_t q = p - n_dst;
       if ((int64_t)q > e) {  // a first occurrence cannot lie after the edge itself
-        atomicOr(&a.st->error, kErrFirstPosLate);
+        report(kErrFirstPosLate);
         a.blk_indices[e] = 0;
         continue;
       }
@@ -178,10 +197,10 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
         if (is_new[k] && local >= 0 && (int64_t)local < a.cap_src) {
           const int64_t g = (int64_t)g_of[k];
           a.S[local] = g_of[k];
-          if (!a.last_hop) a.node_map[g] = a.map_base + local;
+          if (!a.host) a.node_map[g] = a.map_base + local;
           if (a.cache_map) a.S_slot[local] = slot_of[k];
         } else {
-          atomicOr(&a.st->error, kErrNewNode);
+          report(kErrNewNode);
         }
       }
     }

@@ -813,26 +813,7 @@ __device__ __forceinline__ void sample_node_wave(const SampleArgs<IdxT>& a, cons
   }
 }
 
-// ---- lanes of a row of 16, without LDS -----------------------------------------------------------
-// __shfl goes through the LDS unit (some hundred cycles a step); a data-parallel move inside a row
-// of 16 lanes is an operand of an ordinary vector instruction.
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {  // lanes without a source read 0
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, kCtrl, 0xf, 0xf, true);
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;          // quad_perm [1,0,3,2], [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;  // i -> 7 - i in a half row, i -> 15 - i in a row
-constexpr int kDppShr = 0x110, kDppLast = 0x15F;         // lane i from i - n; every lane from lane 15
-
-__device__ __forceinline__ uint32_t row16_incl_scan(uint32_t v) {
-  v += dpp_u32<kDppShr + 1>(v);
-  v += dpp_u32<kDppShr + 2>(v);
-  v += dpp_u32<kDppShr + 4>(v);
-  v += dpp_u32<kDppShr + 8>(v);
-  return v;
-}
-__device__ __forceinline__ uint32_t row16_last(uint32_t v) { return dpp_u32<kDppLast>(v); }
-
+// ---- reductions over a group of lanes, without LDS ------------------------------------------------
 // the largest / smallest value of a group of G lanes, in each of them (after the first two steps a
 // quad agrees, after the third a half row, so a mirror image serves as the exchange)
 template <int G>

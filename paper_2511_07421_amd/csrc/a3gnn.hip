@@ -56,6 +56,7 @@ struct a3_ctx {
   bool last_full_only = false;
   uint64_t* cached_bits = nullptr;  // one bit per node, rebuilt from the device map by every weighted call
   int64_t cached_bits_words = 0;    // (with A3_STATIC_MAP: when the map's pointer or size changes)
+  int32_t n_seen = 0;                 // workgroups of the last k_cached_bits
   int32_t* class_mix_kept = nullptr;  // the weight classes of the map the bitmap was made from (device)
   const int32_t* bits_map = nullptr;  // that map, its size; `bits_stale`: it must be made again
   int64_t bits_nodes = -1;
@@ -65,8 +66,8 @@ struct a3_ctx {
   int32_t* fifo_tiles = nullptr;  // FIFO update: tile sums, then tile offsets
   int64_t fifo_tiles_cap = 0;
   DevState* d_state = nullptr;
-  DevState* h_state = nullptr;      // pinned host copy of the counts, written by the last kernel
-  DevState* h_state_dev = nullptr;  // the same memory as the device addresses it
+  a3::HostState* h_state = nullptr;      // pinned host copy of the counts, written by the last kernel
+  a3::HostState* h_state_dev = nullptr;  // the same memory as the device addresses it
   hipEvent_t sampled = nullptr;     // recorded after the last sampling kernel of a call
   // a3_sample_gather_begin: the rows of the nodes numbered in a hop are retrieved on `side` while
   // the next hop is sampled; made on first use
@@ -365,8 +366,7 @@ int build_cached_bits(a3_ctx* ctx, const int32_t* cache_map, int64_t num_nodes) 
   const unsigned blocks = (unsigned)std::min<int64_t>((words + 15) / 16, kCachedBitsBlocks);
   hipLaunchKernelGGL(a3::k_cached_bits, dim3(blocks), dim3(a3::kTileThreads), 0, ctx->stream, cache_map,
                      num_nodes, ctx->cached_bits, ctx->block_seen);
-  hipLaunchKernelGGL(a3::k_class_mix, dim3(1), dim3(a3::kTileThreads), 0, ctx->stream, ctx->block_seen,
-                     (int)blocks, ctx->d_state, ctx->class_mix_kept);
+  ctx->n_seen = (int32_t)blocks;
   A3_HIP(ctx, hipGetLastError());
   return A3_OK;
 }
@@ -405,6 +405,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
   int rc = ensure_node_map(ctx, num_nodes);
   if (rc != A3_OK) return rc;
 
+  ctx->h_state->late_error = 0;  // no call is pending: nothing on the device writes it
   prof_mark(ctx, 0, 0);
   // A3_STATIC_MAP: the bitmap of cached nodes and the map's weight classes are kept while the
   // caller passes the same map (its contents do not change, by the flag's contract)
@@ -439,7 +440,9 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
     fa.from_seeds = (h == 0 && !validate) ? 1 : 0;
     fa.num_seeds = num_seeds;
     fa.cache_map = cache_map;
-    fa.class_mix_kept = (h == 0 && bits_kept) ? ctx->class_mix_kept : nullptr;
+    fa.class_mix_kept = (h == 0 && weighted && num_nodes > 0) ? ctx->class_mix_kept : nullptr;
+    fa.block_seen = bits_kept ? nullptr : ctx->block_seen;
+    fa.n_seen = ctx->n_seen;
     fa.S_slot = ctx->S_slot;
     fa.S = S;
     fa.node_map = ctx->node_map;
@@ -456,12 +459,12 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
                         f <= (weighted ? kGroupWeightedFanout : kGroupFanout);
     fa.groups = groups ? 1 : 0;
     fa.hub_degree = groups ? kHubDegreeMany : kHubDegreeFew;
-    hipLaunchKernelGGL(a3::k_frontier<IdxT>, dim3(dst_tiles), dim3(a3::kTileThreads), 0, st, fa);
+    hipLaunchKernelGGL(a3::k_frontier<IdxT>, dim3(dst_tiles), dim3(a3::kFrontierThreads), 0, st, fa);
     // few tiles: the consumer scans the tile sums itself and the launch is saved
     const bool fuse_dst = dst_tiles <= (unsigned)a3::kFuseTiles;
     const bool fuse_edges = edge_tiles <= (unsigned)a3::kFuseTiles;
     if (!fuse_dst)
-      hipLaunchKernelGGL(a3::k_scan_tiles, dim3(1), dim3(a3::kTileThreads), 0, st, ctx->tile_sums,
+      hipLaunchKernelGGL(a3::k_scan_tiles, dim3(1), dim3(a3::kScanThreads), 0, st, ctx->tile_sums,
                          ctx->tile_offs, ds, h, 0, ctx->blk_indptr[h]);
     // a2-a4: selection
     {
@@ -555,7 +558,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
                        ctx->node_map, ctx->map_base, ds, h, num_nodes, ctx->first_pos, ctx->local_rank,
                        ctx->tile_sums2);
     if (!fuse_edges)
-      hipLaunchKernelGGL(a3::k_scan_tiles, dim3(1), dim3(a3::kTileThreads), 0, st, ctx->tile_sums2,
+      hipLaunchKernelGGL(a3::k_scan_tiles, dim3(1), dim3(a3::kScanThreads), 0, st, ctx->tile_sums2,
                          ctx->tile_offs2, ds, h, 1, (int32_t*)nullptr);
     a3::RelabelArgs<IdxT> ra;
     ra.gid = gid;
@@ -567,7 +570,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
     ra.st = ds;
     ra.bin_count = ctx->bin_count;
     ra.hop = h;
-    ra.last_hop = h == num_hops - 1 ? 1 : 0;  // nothing follows: the relabel map needs no local ids
+    ra.host = h == num_hops - 1 ? ctx->h_state_dev : nullptr;  // the counts go to the host
     ra.num_nodes = num_nodes;
     ra.cap_src = ctx->cap_dst[ctx->max_hops];
     ra.S = S;
@@ -586,8 +589,6 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
       if (rc != A3_OK) return rc;
     }
   }
-  // the counts go to the host
-  hipLaunchKernelGGL(a3::k_publish, dim3(1), dim3(64), 0, st, ds, ctx->h_state_dev);
   prof_mark(ctx, 0, 1);
   A3_HIP(ctx, hipGetLastError());
   A3_HIP(ctx, hipEventRecord(ctx->sampled, st));
@@ -608,7 +609,8 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
 int sample_finish(a3_ctx* ctx, a3_blocks* out) {
   A3_HIP(ctx, hipEventSynchronize(ctx->sampled));
   ctx->pending = false;
-  const DevState& hs = *ctx->h_state;
+  DevState hs = ctx->h_state->st;
+  hs.error |= ctx->h_state->late_error;
   if (hs.error & (a3::kErrBadSeed | a3::kErrDupSeed)) {
     return fail(ctx, A3_ERR_INPUT,
                 (hs.error & a3::kErrBadSeed) ? "a3_sample_blocks: a seed is outside [0, num_nodes)"
@@ -1015,11 +1017,11 @@ extern "C" int a3_create(a3_ctx** out, int hip_device, void* hip_stream, int64_t
   }
   if (rc == A3_OK) {
     void* hp = nullptr;
-    e = hipHostMalloc(&hp, sizeof(DevState), hipHostMallocMapped);
+    e = hipHostMalloc(&hp, sizeof(a3::HostState), hipHostMallocMapped);
     if (e != hipSuccess)
       rc = hip_fail(ctx, e, "a3_create: hipHostMalloc");
     else
-      ctx->h_state = (DevState*)hp;
+      ctx->h_state = (a3::HostState*)hp;
   }
   if (rc == A3_OK) {
     void* dp = nullptr;
@@ -1027,7 +1029,7 @@ extern "C" int a3_create(a3_ctx** out, int hip_device, void* hip_stream, int64_t
     if (e != hipSuccess)
       rc = hip_fail(ctx, e, "a3_create: hipHostGetDevicePointer");
     else
-      ctx->h_state_dev = (DevState*)dp;
+      ctx->h_state_dev = (a3::HostState*)dp;
   }
   if (rc == A3_OK) {
     e = hipEventCreateWithFlags(&ctx->sampled, hipEventDisableTiming);
@@ -1184,7 +1186,7 @@ extern "C" int a3_sample_stats(a3_ctx* ctx, int64_t stats[5]) {
     return fail(ctx, A3_ERR_HIP, "a3_sample_stats: context was created without a device");
   if (ctx->pending || ctx->last_hops == 0)
     return fail(ctx, A3_ERR_INVALID_ARG, "a3_sample_stats: no ended call to report on");
-  const DevState& hs = *ctx->h_state;
+  const DevState& hs = ctx->h_state->st;
   stats[0] = hs.class_mix;
   stats[1] = hs.n_deferred[0];
   stats[2] = hs.n_deferred[1];
