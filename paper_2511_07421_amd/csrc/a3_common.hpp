@@ -13,6 +13,7 @@ constexpr int kTileThreads = 256;
 constexpr int kTilePerThread = 4;
 constexpr int kTile = kTileThreads * kTilePerThread;  // elements per scan tile
 constexpr int kTileShift = 10;
+constexpr int kSmallTileShift = 8;   // node tiles of small frontiers (see k_frontier)
 
 constexpr int32_t kErrBadSeed = 1;  // seed outside [0, num_nodes)
 constexpr int32_t kErrDupSeed = 2;  // a seed appears twice

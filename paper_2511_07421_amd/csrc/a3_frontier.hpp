@@ -85,11 +85,12 @@ __device__ __forceinline__ int degree_bin(uint32_t deg, bool groups, uint32_t hu
 // One thread per node of the tile: with four nodes per thread the single workgroup of a small
 // frontier, one wavefront per SIMD, went through four times the instructions one after the other
 // (256 nodes 6.7 -> 3.9 us, 1 024 nodes 13.3 -> 11.5, 20 k nodes 10.4 -> 7.3).
-constexpr int kFrontierThreads = kTile;
-
-template <typename IdxT>
-__global__ __launch_bounds__(kFrontierThreads) void k_frontier(const FrontierArgs<IdxT> a) {
-  __shared__ uint32_t lds[kFrontierThreads / kWave];
+// Two sizes of tile: small frontiers are cut into tiles of 256 nodes, since a node's random accesses
+// (row bounds, relabel map, device map) miss the L1 and one CU gets through some hundred of them
+// per microsecond (1 024 seeds: 11.5 us as one tile, 6.1 as four; 4 096 seeds 11.3 and 7.8).
+template <typename IdxT, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_frontier(const FrontierArgs<IdxT> a) {
+  __shared__ uint32_t lds[kThreads / kWave];
   __shared__ uint32_t bin_n[16];
   __shared__ uint32_t bin_base[kNumBins];
   __shared__ uint32_t seen_lds;
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kFrontierThreads) void k_frontier(const FrontierArg
   if (a.class_mix_kept && blockIdx.x == 0) {
     if (a.block_seen) {
       uint32_t seen = 0;
-      for (int b = threadIdx.x; b < a.n_seen; b += kFrontierThreads) seen |= (uint32_t)a.block_seen[b];
+      for (int b = threadIdx.x; b < a.n_seen; b += kThreads) seen |= (uint32_t)a.block_seen[b];
       const uint32_t wave_seen = (__ballot(seen & 1u) ? 1u : 0u) | (__ballot(seen & 2u) ? 2u : 0u);
       if (lane_id() == 0 && wave_seen) atomicOr(&seen_lds, wave_seen);
       __syncthreads();
@@ -111,8 +112,8 @@ __global__ __launch_bounds__(kFrontierThreads) void k_frontier(const FrontierArg
   }
   if (from_seeds && blockIdx.x == 0 && threadIdx.x == 0) a.st->n_dst[0] = (int32_t)a.num_seeds;
   const int64_t n = from_seeds ? a.num_seeds : (int64_t)a.st->n_dst[a.hop];
-  if ((int64_t)blockIdx.x * kTile >= n) return;
-  const int64_t i = (int64_t)blockIdx.x * kTile + threadIdx.x;
+  if ((int64_t)blockIdx.x * kThreads >= n) return;
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   uint32_t cnt = 0, bin = 15;  // 15: no node
   NodeRec rec = {};
   if (i < n) {
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(kFrontierThreads) void k_frontier(const FrontierArg
   if (in_wave == 0) reserved = atomicAdd(&bin_n[bin], (uint32_t)__popcll(same));
   const uint32_t rank = (uint32_t)__shfl((int)reserved, __ffsll((long long)same) - 1, kWave) + in_wave;
   uint32_t total;
-  const uint32_t local_off = block_excl_scan<kFrontierThreads>(cnt, lds, &total);
+  const uint32_t local_off = block_excl_scan<kThreads>(cnt, lds, &total);
   // one global reservation per bin and block, then scatter the node records
   if (threadIdx.x < kNumBins)
     bin_base[threadIdx.x] = bin_n[threadIdx.x]

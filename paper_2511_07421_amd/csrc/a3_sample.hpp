@@ -16,6 +16,7 @@ struct SampleArgs {
   const int32_t* tile_offs;  // scanned tile offsets in global memory, or null: scan tile_sums here
   const int32_t* tile_sums;
   int64_t cap_tiles;         // the launch's bound on the tiles in use (at most the entries of tile_sums)
+  int32_t tile_shift;        // log2 of the nodes per tile
   int32_t* blk_indptr;       // out: edge offsets of this hop
   IdxT* gid;                 // out: global id of each sampled neighbour
   int64_t* eids;             // out: CSR position of each sampled edge (may be null)
@@ -552,7 +553,7 @@ __device__ __forceinline__ void sample_node_wave(const SampleArgs<IdxT>& a, cons
   const int64_t i = r.i;
   const uint32_t deg = r.deg;
   const uint32_t f = (uint32_t)a.fanout;
-  const int32_t base = tile_offs[i >> kTileShift] + r.local_off;
+  const int32_t base = tile_offs[i >> a.tile_shift] + r.local_off;
   if (lane == 0) a.blk_indptr[i] = base;
   const Emitter<IdxT> emit{a, row, base, n_dst};
 
@@ -926,7 +927,7 @@ __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, con
   const int64_t row = r.row;
   const uint32_t deg = live ? r.deg : 0;  // <= 4 G by construction of the bins
   const uint32_t m = (uint32_t)a.fanout;
-  const int32_t base = live ? tile_offs[r.i >> kTileShift] + r.local_off : 0;
+  const int32_t base = live ? tile_offs[r.i >> a.tile_shift] + r.local_off : 0;
   if (live && gl == 0) a.blk_indptr[r.i] = base;
   const bool draw = deg > m;  // else every neighbour is kept
   const PhiloxKey pk{(uint32_t)(uint64_t)v, (uint32_t)((uint64_t)v >> 32), (uint32_t)a.hop,
@@ -1136,7 +1137,7 @@ __device__ __forceinline__ bool sample_node_16(const SampleArgs<IdxT>& a, const 
   uint32_t* slots = keys + kListStride;
   const uint32_t deg = live ? r.deg : 0;
   const uint32_t m = (uint32_t)a.fanout;
-  const int32_t base = live ? tile_offs[r.i >> kTileShift] + r.local_off : 0;
+  const int32_t base = live ? tile_offs[r.i >> a.tile_shift] + r.local_off : 0;
   if (live && gl == 0) a.blk_indptr[r.i] = base;
   const bool whole = deg <= m;  // every neighbour is kept
   bool open = !whole;
@@ -1417,7 +1418,7 @@ __global__ __launch_bounds__(kSampleMaxThreads) __attribute__((amdgpu_waves_per_
   const int32_t n_dst = a.st->n_dst[a.hop];
   const bool both_classes = kMode != kUniform && a.st->class_mix == 3;  // read once, not per node
   if (tile_offs == nullptr) {  // few tiles: scan the tile sums here, publish the hop's edge count
-    const uint32_t total = tile_prefix_from(sums, a.cap_tiles, ((int64_t)n_dst + kTile - 1) >> kTileShift,
+    const uint32_t total = tile_prefix_from(sums, a.cap_tiles, ((int64_t)n_dst + (1 << a.tile_shift) - 1) >> a.tile_shift,
                                             fused_offs, &fused_total);
     tile_offs = fused_offs;
     if (blockIdx.x == 0 && threadIdx.x == 0) {

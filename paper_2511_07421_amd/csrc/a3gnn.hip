@@ -147,6 +147,9 @@ uint32_t cap_for(uint32_t lambda) { return ((2 * lambda + 63) / 64) * 64; }
 constexpr int64_t kFullOnlyShare = 5;
 constexpr int kFullOnlyCalls = 16;
 uint32_t lambda_for_first_list(int32_t m) { return (uint32_t)(m + 6.0 * std::sqrt((double)m) + 12.0); }
+// Frontiers of up to this many nodes are cut into tiles of 256, larger ones of 1 024: at most 64
+// tile sums, one per lane of the wavefront that scans them in every k_sample workgroup.
+constexpr int64_t kSmallTileNodes = 16384;
 constexpr int64_t kMaxRoleWaves = 8192;  // wavefronts serving one role of k_sample
 constexpr int64_t kMaxHubBlocks = 2048;
 constexpr int kSampleWaves = 4;           // wavefronts per k_sample workgroup (fewer if LDS is short)
@@ -432,7 +435,8 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
 
   for (int h = 0; h < num_hops; ++h) {
     const int32_t f = fanouts[h];
-    const unsigned dst_tiles = blocks_for(bound_dst[h], a3::kTile);
+    const int tile_shift = bound_dst[h] <= kSmallTileNodes ? a3::kSmallTileShift : a3::kTileShift;
+    const unsigned dst_tiles = blocks_for(bound_dst[h], 1 << tile_shift);
     const unsigned edge_tiles = blocks_for(bound_edges[h], a3::kTile);
     // a1: degrees -> edge offsets of the block, degree bins
     a3::FrontierArgs<IdxT> fa;
@@ -459,7 +463,11 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
                         f <= (weighted ? kGroupWeightedFanout : kGroupFanout);
     fa.groups = groups ? 1 : 0;
     fa.hub_degree = groups ? kHubDegreeMany : kHubDegreeFew;
-    hipLaunchKernelGGL(a3::k_frontier<IdxT>, dim3(dst_tiles), dim3(a3::kFrontierThreads), 0, st, fa);
+    if (tile_shift == a3::kSmallTileShift)
+      hipLaunchKernelGGL((a3::k_frontier<IdxT, 1 << a3::kSmallTileShift>), dim3(dst_tiles),
+                         dim3(1 << a3::kSmallTileShift), 0, st, fa);
+    else
+      hipLaunchKernelGGL((a3::k_frontier<IdxT, a3::kTile>), dim3(dst_tiles), dim3(a3::kTile), 0, st, fa);
     // few tiles: the consumer scans the tile sums itself and the launch is saved
     const bool fuse_dst = dst_tiles <= (unsigned)a3::kFuseTiles;
     const bool fuse_edges = edge_tiles <= (unsigned)a3::kFuseTiles;
@@ -476,6 +484,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
       sa.tile_offs = fuse_dst ? nullptr : ctx->tile_offs;
       sa.tile_sums = ctx->tile_sums;
       sa.cap_tiles = std::min<int64_t>(ctx->cap_tiles, dst_tiles);
+      sa.tile_shift = tile_shift;
       sa.blk_indptr = ctx->blk_indptr[h];
       sa.gid = gid;
       sa.eids = ctx->blk_eids[h];
@@ -969,7 +978,7 @@ extern "C" int a3_create(a3_ctx** out, int hip_device, void* hip_stream, int64_t
     return rc;
   }
   const int64_t max_items = std::max(max_edges, ctx->cap_dst[max_hops]);
-  ctx->cap_tiles = (max_items + a3::kTile - 1) / a3::kTile + 1;
+  ctx->cap_tiles = std::max<int64_t>((max_items + a3::kTile - 1) / a3::kTile + 1, kSmallTileNodes >> a3::kSmallTileShift);
   int rc = A3_OK;
   {
     // set-up, once per device: where this device keeps the static scratch of
