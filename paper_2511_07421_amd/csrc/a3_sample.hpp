@@ -850,6 +850,23 @@ __device__ __forceinline__ uint64_t group_min_u64(uint64_t v) {
   return v;
 }
 
+// The key -log2(u) / w in single precision, as bits that compare like the value (it is not negative).
+// Against the exact key in Q32 it is off by at most 0.12 kKeyError (1 + key): the largest error over all
+// 2^32 draws; dividing by the weight adds 2^-23 of the key.  Where the m-th best key and the next lie
+// further apart than twice kKeyError each, the choice is the exact keys'; elsewhere (one node in some
+// hundreds) those decide.  An exact key takes 32 dependent multiply-shift steps, 200 instructions;
+// this one takes six (third hop of 237 k nodes: 174 -> 147 us).
+constexpr float kKeyError = 0x1p-20f;
+__device__ __forceinline__ uint32_t approx_key(uint32_t x, float inv_w) {
+  const float u = __builtin_fmaf((float)x, 0x1p-32f, 0x1p-32f);  // (x + 1) / 2^32
+  return __float_as_uint(__builtin_fabsf(__builtin_amdgcn_logf(u)) * inv_w);
+}
+// may exact keys order these two the other way?  (next: ~0 for none)
+__device__ __forceinline__ bool keys_too_close(uint32_t last, uint32_t next) {
+  const float l = __uint_as_float(last);
+  return next != ~0u && __uint_as_float(next) - l <= 4.0f * kKeyError * (1.0f + l);
+}
+
 // ---- edges of the lane groups ---------------------------------------------------------------------
 // A group's chosen slots stand in LDS, in order, k of them; consecutive lanes write consecutive edges.
 // All neighbour ids of a group are asked for before the first is used; where one round of the lanes
@@ -912,8 +929,8 @@ __device__ __forceinline__ void put_list(const SampleArgs<IdxT>& a, int64_t row,
 // ---- a group of G lanes (4 or 8), one node of degree <= 4 G: four slots per lane -----------------
 // The draws of a lane are one Philox block.  Selection is m rounds of "best remaining slot of the
 // group" on 32-bit keys: lane-local minimum, reduction over the group, every slot that has the
-// minimum is out.  Equal keys (weighted: keys that agree in their upper 32 bits) leave more than m
-// chosen; the choice is then made again in full precision, one slot per round, all ties resolved.
+// minimum is out.  Equal keys leave more than m chosen; then, and where single-precision keys leave the
+// cut open, the choice is made again in full precision, one slot per round, all ties resolved.
 template <typename IdxT, int G, int kMode>
 __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, const int32_t* tile_offs,
                                                   const NodeRec& r, bool live, int32_t n_dst, uint32_t* lds,
@@ -969,16 +986,19 @@ __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, con
       own[w] = ~0u;
       if (alive & (1u << w)) {
         own[w] = ~x[w];
-        if (kMode != kUniform && mixed)  // K < 2^38: its upper 32 bits
-          own[w] = (uint32_t)(sample_key(x[w], cached[w] ? a.bias_q16 : 65536u, cached[w] ? a.inv_bias : kInvOne) >> 6);
+        if (kMode != kUniform && mixed) own[w] = approx_key(x[w], cached[w] ? (float)a.inv_bias * 65536.0f : 1.0f);
       }
     }
+    uint32_t last = 0;
 #pragma unroll 1
     for (uint32_t it = 0; it < m; ++it) {
-      const uint32_t best = group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3])));
+      last = group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3])));
 #pragma unroll
-      for (int w = 0; w < 4; ++w) own[w] = own[w] == best ? ~0u : own[w];
+      for (int w = 0; w < 4; ++w) own[w] = own[w] == last ? ~0u : own[w];
     }
+    bool close = false;
+    if (kMode != kUniform && __ballot(mixed))
+      close = mixed && keys_too_close(last, group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3]))));
     uint32_t in_rounds = 0, n_chosen = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -987,7 +1007,7 @@ __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, con
       n_chosen += (uint32_t)__popcll(__ballot((in_rounds >> w) & 1u) & group_lanes);
     }
     if (draw) chosen = in_rounds;
-    const bool tie = draw && n_chosen != m;
+    const bool tie = draw && (n_chosen != m || close);
     if (__ballot(tie)) {
       uint64_t K[4] = {0, 0, 0, 0};
       uint32_t rest = alive, picked = 0;
@@ -1044,7 +1064,7 @@ __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, con
 // their slots.  With at most kListCap candidates a lane holds up to four of them in registers; the m
 // smallest are taken out in m rounds of a minimum over the sixteen lanes (9 to 15 instructions a
 // round for four nodes).  A chosen candidate's output position is a scan of the chosen ones before it.
-// Equal keys leave more than m chosen (weighted: keys that agree in their upper 32 bits): such a
+// Equal keys leave more than m chosen (weighted: exact keys that agree in their upper 32 bits): such a
 // node, and one whose list came out too short or too long, is left to the wavefront path (false).
 // Weighted: the list decides as in weighted_from_first_list (at least m of it cached), or if it holds
 // the whole neighbourhood; rows of up to 64 get a second attempt with exactly that.
@@ -1069,13 +1089,13 @@ __device__ __forceinline__ bool finish_list(const SampleArgs<IdxT>& a, int64_t r
     if (good && at < cnt) own[k] = keys[at];  // below ~0: the threshold is at least 1
     slot[k] = slots[at];
   }
-  bool decided = good;
+  bool decided = good, mixed = false;
   IdxT u[NK];
+  bool cached[NK];
   if (kMode != kUniform && both_classes) {
 #pragma unroll
     for (int k = 0; k < NK; ++k)
       if (own[k] != ~0u) u[k] = a.indices[row + slot[k]];
-    bool cached[NK];
     uint32_t n_c = 0;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
@@ -1084,30 +1104,47 @@ __device__ __forceinline__ bool finish_list(const SampleArgs<IdxT>& a, int64_t r
     }
     n_c = row16_last(row16_incl_scan(n_c));
     decided = good && (n_c >= m || cnt == deg);
-    const bool mixed = decided && n_c != 0 && n_c != cnt;  // else the keys are monotone in the draws
-    if (__ballot(mixed)) {
+    mixed = decided && n_c != 0 && n_c != cnt;  // else the keys are monotone in the draws
 #pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        if (mixed && own[k] != ~0u) {
-          // K < 2^38: its upper 32 bits
-          own[k] = (uint32_t)(sample_key(~own[k], cached[k] ? a.bias_q16 : 65536u, cached[k] ? a.inv_bias : kInvOne) >> 6);
-        }
-      }
-    }
-  }
-#pragma unroll 1
-  for (uint32_t it = 0; it < m; ++it) {
-    uint32_t best = own[0];
-#pragma unroll
-    for (int k = 1; k < NK; ++k) best = min(best, own[k]);
-    best = group_min_u32<16>(best);
-#pragma unroll
-    for (int k = 0; k < NK; ++k) own[k] = own[k] == best ? ~0u : own[k];
+    for (int k = 0; k < NK; ++k)
+      if (mixed && own[k] != ~0u) own[k] = approx_key(~own[k], cached[k] ? (float)a.inv_bias * 65536.0f : 1.0f);
   }
   uint32_t mine = 0;  // a byte per k: the lane's candidate is chosen
+  bool open = good;
+  for (int pass = 0;; ++pass) {
+    uint32_t best = 0;
+#pragma unroll 1
+    for (uint32_t it = 0; it < m; ++it) {
+      best = own[0];
 #pragma unroll
-  for (int k = 0; k < NK; ++k)
-    mine |= (good && (uint32_t)k * 16u + gl < cnt && own[k] == ~0u) ? 1u << (8 * k) : 0u;
+      for (int k = 1; k < NK; ++k) best = min(best, own[k]);
+      best = group_min_u32<16>(best);
+#pragma unroll
+      for (int k = 0; k < NK; ++k) own[k] = own[k] == best ? ~0u : own[k];
+    }
+    uint32_t chosen = 0;
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+      chosen |= ((uint32_t)k * 16u + gl < cnt && own[k] == ~0u) ? 1u << (8 * k) : 0u;
+    if (open) mine = chosen;
+    if (kMode == kUniform || pass != 0 || __ballot(mixed) == 0) break;
+    // groups whose cut the single-precision keys leave open choose again, by the upper 32 bits of the
+    // exact keys (K < 2^38)
+    uint32_t next = own[0];
+#pragma unroll
+    for (int k = 1; k < NK; ++k) next = min(next, own[k]);
+    next = group_min_u32<16>(next);
+    const uint32_t n_chosen = (row16_last(row16_incl_scan(chosen)) * 0x01010101u) >> 24;
+    open = mixed && (n_chosen != m || keys_too_close(best, next));
+    if (__ballot(open) == 0) break;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const uint32_t at = (uint32_t)k * 16u + gl;
+      own[k] = ~0u;
+      if (open && at < cnt)
+        own[k] = (uint32_t)(sample_key(~keys[at], cached[k] ? a.bias_q16 : 65536u, cached[k] ? a.inv_bias : kInvOne) >> 6);
+    }
+  }
   const uint32_t incl = row16_incl_scan(mine);
   const uint32_t total = row16_last(incl);
   const bool done = decided && (total * 0x01010101u) >> 24 == m;  // the sum of the bytes
