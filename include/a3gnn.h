@@ -66,7 +66,7 @@ extern "C" {
                                 through this context's own a3_cache_fifo_update*: what a weighted call
                                 derives from the map (a bitmap of the cached nodes, the weight classes
                                 present: Sec. III-A) is then made when the pointer or num_nodes changes
-                                instead of at every call (two kernels, 10 us at 2.45 M nodes).  A change
+                                instead of at every call (a kernel of 6 us at 2.45 M nodes).  A change
                                 the context cannot see (the caller rewrote the map, or freed it and
                                 built another at the same address) is announced with
                                 a3_device_map_changed */
