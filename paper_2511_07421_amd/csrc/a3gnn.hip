@@ -417,11 +417,9 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
     bits_kept = (ctx->flags & A3_STATIC_MAP) && !ctx->bits_stale && ctx->bits_map == cache_map &&
                 ctx->bits_nodes == num_nodes;
     if (!bits_kept) {
+      ctx->bits_stale = true;  // until the whole call is queued: hop 0's k_frontier writes the classes
       rc = build_cached_bits(ctx, cache_map, num_nodes);
       if (rc != A3_OK) return rc;
-      ctx->bits_map = cache_map;
-      ctx->bits_nodes = num_nodes;
-      ctx->bits_stale = false;
     }
   }
   if (validate) {
@@ -601,6 +599,11 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
   prof_mark(ctx, 0, 1);
   A3_HIP(ctx, hipGetLastError());
   A3_HIP(ctx, hipEventRecord(ctx->sampled, st));
+  if (weighted && !bits_kept) {
+    ctx->bits_map = cache_map;
+    ctx->bits_nodes = num_nodes;
+    ctx->bits_stale = false;
+  }
   ctx->pending = true;
   ctx->last_hops = num_hops;
   ctx->last_idx_bytes = (int32_t)sizeof(IdxT);
