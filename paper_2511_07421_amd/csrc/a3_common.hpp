@@ -51,11 +51,14 @@ struct DevState {
 };
 
 // The host's copy (pinned memory), written by the call's last kernel: the state block as that kernel
-// found it, with its own counts, and the error bits that it raises itself.
+// found it, with its own counts, and the guards that it trips itself: a word for each of the three bits
+// from kErrFirstPosNeg on, so that plain stores of many workgroups lose none (an atomic on host memory
+// would rest on the link's support for it).
 struct HostState {
   DevState st;
-  int32_t late_error;
+  int32_t late_error[3];
 };
+static_assert(kErrFirstPosLate == kErrFirstPosNeg << 1 && kErrNewNode == kErrFirstPosNeg << 2, "late_error: a word per bit");
 
 // What k_sample needs to know of a frontier node; k_frontier has it all in registers and writes
 // it into the node's degree bin, so that the sampler starts a node with one 32-byte load instead

@@ -108,7 +108,8 @@ __global__ __launch_bounds__(kTileThreads) void k_relabel(const RelabelArgs<IdxT
   const bool fuse = a.tile_offs == nullptr;
   auto report = [&](int32_t bit) {
     if (a.host)
-      __hip_atomic_store(&a.host->late_error, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&a.host->late_error[__builtin_ctz(bit / kErrFirstPosNeg)], bit, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
     else
       atomicOr(&a.st->error, bit);
   };

@@ -408,7 +408,7 @@ int sample_enqueue(a3_ctx* ctx, const int64_t* indptr, const IdxT* indices, int6
   int rc = ensure_node_map(ctx, num_nodes);
   if (rc != A3_OK) return rc;
 
-  ctx->h_state->late_error = 0;  // no call is pending: nothing on the device writes it
+  for (int32_t& e : ctx->h_state->late_error) e = 0;  // no call is pending: nothing on the device writes them
   prof_mark(ctx, 0, 0);
   // A3_STATIC_MAP: the bitmap of cached nodes and the map's weight classes are kept while the
   // caller passes the same map (its contents do not change, by the flag's contract)
@@ -622,7 +622,7 @@ int sample_finish(a3_ctx* ctx, a3_blocks* out) {
   A3_HIP(ctx, hipEventSynchronize(ctx->sampled));
   ctx->pending = false;
   DevState hs = ctx->h_state->st;
-  hs.error |= ctx->h_state->late_error;
+  for (const int32_t e : ctx->h_state->late_error) hs.error |= e;
   if (hs.error & (a3::kErrBadSeed | a3::kErrDupSeed)) {
     return fail(ctx, A3_ERR_INPUT,
                 (hs.error & a3::kErrBadSeed) ? "a3_sample_blocks: a seed is outside [0, num_nodes)"

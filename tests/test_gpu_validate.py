@@ -111,3 +111,24 @@ def test_planted_mistakes_in_the_device_map_are_named():
     ctx.validate_cache_map(split.cache_map.to(DEV), n_dev, n_host)
     ctx.validate_cache_map(split.cache_map.to(DEV), n_dev + 9, n_host + 9)   # stores may be larger
     ctx.close()
+
+
+def test_guards_of_a_calls_last_kernel_are_all_reported():
+    """Two different guards of the last relabelling kernel trip in one call: ids outside the graph are never
+    followed, and the message holds the bits of both (32, 64) beside the sampler's own (256).  A3_TEST_MAP_RANGE
+    has the third call refill the relabel map, so what is left in the edge list there is known: edges 0 and 1 keep
+    the ids 4 and 5 of the call before, of which 4 is met again at edge 2 and 5 is not."""
+    ctx = a3.Context(2, [2], flags=a3.A3_TEST_MAP_RANGE)
+    indptr = torch.tensor([0, 2, 4] + [4] * 6, dtype=torch.int64, device=DEV)
+    seeds = torch.tensor([0, 1], dtype=torch.int32, device=DEV)
+    good = torch.tensor([4, 5, 6, 7], dtype=torch.int32, device=DEV)
+    bad = torch.tensor([8, -1, 4, 7], dtype=torch.int32, device=DEV)
+    for _ in range(2):
+        assert ctx.sample_blocks(indptr, good, seeds, [2]).n_edges == [4]
+    print("[case] two ids outside the graph", flush=True)
+    with pytest.raises(a3.A3Error) as ei:
+        ctx.sample_blocks(indptr, bad, seeds, [2])
+    assert ei.value.code == a3.A3_ERR_HIP and f"guard bits {256 | 64 | 32})" in str(ei.value), str(ei.value)
+    got = ctx.sample_blocks(indptr, good, seeds, [2]).to_host()   # the context recovers
+    assert got.input_nodes.tolist() == [0, 1, 4, 5, 6, 7] and got.blk_indices[0].tolist() == [2, 3, 4, 5]
+    ctx.close()
