@@ -1380,14 +1380,22 @@ __global__ __launch_bounds__(kSampleMaxThreads) __attribute__((amdgpu_waves_per_
   // Workgroups start in index order, so the roles whose workgroups run longest come first (hubs, then
   // the lane groups, which have a dozen nodes' chains each) and the single wide nodes fill the end
   // of the launch (wide nodes before the groups: hop 3 of a mini-batch 214 instead of 199 us at 616 k
-  // nodes, 294 instead of 289 at 337 k).
+  // nodes, 294 instead of 289 at 337 k).  In the only launch of a weighted hop the groups have rows of up
+  // to 64 neighbours and every longer one is a wide node, scanned twice or three times: there the wide
+  // nodes come first (16 384 seeds, three hops, one node in ten cached, bias rate 4: 1 095 us a call, with
+  // the groups first 1 157; bias rate 1 000: 2 860 and 2 950).
   uint32_t b = blockIdx.x;
   const bool hub_role = b < a.hub_blocks;  // the same for the whole workgroup
   bool group_role = false;
   if (!hub_role) {
     b -= a.hub_blocks;
-    group_role = b < a.group_blocks;
-    if (!group_role) b -= a.group_blocks;
+    if (kMode == kWeightedFull) {
+      group_role = b >= a.wide_blocks;
+      if (group_role) b -= a.wide_blocks;
+    } else {
+      group_role = b < a.group_blocks;
+      if (!group_role) b -= a.group_blocks;
+    }
   }
   // the wavefront's index inside the workgroup, held in a scalar register so that the node loops
   // below are uniform control flow for the whole wavefront
