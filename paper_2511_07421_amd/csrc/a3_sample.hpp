@@ -853,9 +853,13 @@ __device__ __forceinline__ uint64_t group_min_u64(uint64_t v) {
 // The key -log2(u) / w in single precision, as bits that compare like the value (it is not negative).
 // Against the exact key in Q32 it is off by at most 0.12 kKeyError (1 + key): the largest error over all
 // 2^32 draws; dividing by the weight adds 2^-23 of the key.  Where the m-th best key and the next lie
-// further apart than twice kKeyError each, the choice is the exact keys'; elsewhere (one node in some
-// hundreds) those decide.  An exact key takes 32 dependent multiply-shift steps, 200 instructions;
-// this one takes six (third hop of 237 k nodes: 174 -> 147 us).
+// further apart than twice kKeyError each, the choice is the exact keys'.  Nearer ones are looked at
+// again: the keys of cached neighbours, and with them their errors, are 1 / w of an uncached one's, so
+// where no uncached neighbour is near the cut, a w-th of that distance is enough.  What is still open (one
+// node in some hundreds, at any bias rate) the exact keys decide.  An exact key takes 32 dependent
+// multiply-shift steps, 200 instructions; this one takes six (third hop of 237 k nodes: 174 -> 147 us;
+// without the second look a call on 16 384 seeds with half of the nodes cached takes 650 us at bias rate
+// 1 000 and 915 at 60 000, by exact keys alone 698 and 888, with it 581 and 608).
 constexpr float kKeyError = 0x1p-20f;
 __device__ __forceinline__ uint32_t approx_key(uint32_t x, float inv_w) {
   const float u = __builtin_fmaf((float)x, 0x1p-32f, 0x1p-32f);  // (x + 1) / 2^32
@@ -865,6 +869,17 @@ __device__ __forceinline__ uint32_t approx_key(uint32_t x, float inv_w) {
 __device__ __forceinline__ bool keys_too_close(uint32_t last, uint32_t next) {
   const float l = __uint_as_float(last);
   return next != ~0u && __uint_as_float(next) - l <= 4.0f * kKeyError * (1.0f + l);
+}
+// the same for two cached neighbours (2^-30: the exact keys end at 2^-32)
+__device__ __forceinline__ bool cached_keys_too_close(uint32_t last, uint32_t next, float inv_w) {
+  const float l = __uint_as_float(last);
+  return __uint_as_float(next) - l <= 4.0f * kKeyError * (inv_w + l) + 0x1p-30f;
+}
+// may an uncached neighbour that drew x belong on the other side of a cut at `last`, whose next key is
+// too close to it?
+__device__ __forceinline__ bool uncached_near_cut(uint32_t x, uint32_t last) {
+  const float l = __uint_as_float(last);
+  return __builtin_fabsf(__uint_as_float(approx_key(x, 1.0f)) - l) <= 8.0f * kKeyError * (1.0f + l);
 }
 
 // ---- edges of the lane groups ---------------------------------------------------------------------
@@ -997,8 +1012,17 @@ __device__ __forceinline__ void sample_node_group(const SampleArgs<IdxT>& a, con
       for (int w = 0; w < 4; ++w) own[w] = own[w] == last ? ~0u : own[w];
     }
     bool close = false;
-    if (kMode != kUniform && __ballot(mixed))
-      close = mixed && keys_too_close(last, group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3]))));
+    if (kMode != kUniform && __ballot(mixed)) {
+      const uint32_t next = group_min_u32<G>(min(min(own[0], own[1]), min(own[2], own[3])));
+      close = mixed && keys_too_close(last, next);
+      if (__ballot(close)) {
+        bool near_cut = false;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) near_cut |= (alive & (1u << w)) && !cached[w] && uncached_near_cut(x[w], last);
+        close = close && ((__ballot(near_cut) & group_lanes) != 0 ||
+                          cached_keys_too_close(last, next, (float)a.inv_bias * 65536.0f));
+      }
+    }
     uint32_t in_rounds = 0, n_chosen = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -1136,6 +1160,15 @@ __device__ __forceinline__ bool finish_list(const SampleArgs<IdxT>& a, int64_t r
     next = group_min_u32<16>(next);
     const uint32_t n_chosen = (row16_last(row16_incl_scan(chosen)) * 0x01010101u) >> 24;
     open = mixed && (n_chosen != m || keys_too_close(best, next));
+    if (__ballot(open) == 0) break;
+    bool near_cut = false;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const uint32_t at = (uint32_t)k * 16u + gl;
+      near_cut |= open && at < cnt && !cached[k] && uncached_near_cut(~keys[at], best);
+    }
+    const bool any_near = row16_last(row16_incl_scan(near_cut ? 1u : 0u)) != 0;
+    open = open && (n_chosen != m || any_near || cached_keys_too_close(best, next, (float)a.inv_bias * 65536.0f));
     if (__ballot(open) == 0) break;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
