@@ -21,7 +21,7 @@ DEV = "cuda:0"
 def test_error_of_the_single_precision_keys(gamma):
     """Two keys are told apart from 4 (1 / w + key) kKeyError on: 2 for each of them.  Expected: 0.12 for the
     logarithm and 2^-23 / 2^-20 = 0.125 for the division by the weight (a rounded reciprocal and a product).
-    Sixteenfold room is left below the limit."""
+    At least eightfold room is left below the limit."""
     lib = C.CDLL(native.build(force=False))
     lib.key_error.argtypes = [C.c_uint32, C.c_uint32, C.c_void_p, C.c_void_p]
     blocks = 8192
