@@ -180,10 +180,12 @@ int a3_sample_blocks_end(a3_ctx* ctx, a3_blocks* out);
  * rate and the cache decide how often the weights matter).  stats (host) receives
  *   [0] weight classes met in the device map: bit 0 some node cached, bit 1 some node not
  *       (0 for a call without weights; 3 = the weighted selection was in use);
- *   [1] wide nodes (65 ... 4096 neighbours) and [2] hubs that the first sampling launch of a hop
- *       could not decide from their best draws alone (fewer than `fanout` cached among them, or odd
- *       list sizes) and left to the slower second launch;
- *   [3] nodes selected by the exhaustive bit-by-bit path (about one in 10^5 by design);
+ *   [1] nodes of more than 32 neighbours and [2] hubs (above 4096 neighbours, in large hops above
+ *       8192) that the first sampling launch of a hop could not decide from their best draws alone
+ *       (fewer than `fanout` cached among them, or odd list sizes) and left to the slower second
+ *       launch;
+ *   [3] nodes selected by the exhaustive bit-by-bit path (practically none: about one node in 10^5
+ *       has too few draws above the threshold and is scanned a second time first);
  *   [4] the launch plan of that call: 0 no weights, 1 two launches per hop (the fast one, then
  *       the one for what it left over), 2 one full launch per hop.  A context switches to plan 2
  *       for its next 16 weighted calls when [1] + [2] exceeds a fifth of the call's frontier

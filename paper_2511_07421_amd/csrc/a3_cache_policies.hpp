@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fifo_flag(const IdxT* __restri
     sum += miss[k];
   }
   uint32_t total;
-  uint32_t before = block_excl_scan_256(sum, lds4, &total);
+  uint32_t before = block_excl_scan<kTileThreads>(sum, lds4, &total);
 #pragma unroll
   for (int k = 0; k < kTilePerThread; ++k) {
     const int64_t i = base_i + k;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fifo_scan(const int32_t* __res
     const int64_t t = t0 + threadIdx.x;
     const uint32_t v = t < n_tiles ? (uint32_t)tile_sums[t] : 0u;
     uint32_t total;
-    const uint32_t ex = block_excl_scan_256(v, lds4, &total);
+    const uint32_t ex = block_excl_scan<kTileThreads>(v, lds4, &total);
     if (t < n_tiles) tile_offs[t] = (int32_t)(carry + ex);
     carry += total;
   }

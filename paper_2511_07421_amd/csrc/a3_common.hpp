@@ -25,9 +25,9 @@ constexpr int32_t kErrInternal = 8 | 16 | 32 | 64 | 128 | 256;
 
 // Frontier nodes by degree.  0: deg <= 16, 1: <= 32 (groups of 4, 8 lanes, four slots per lane);
 // 2: <= 64, 3: <= 128, ... 7: <= kGroupDegree (groups of 16 lanes, 64 slots per step; a wavefront's
-// four nodes come from one bin, so their rows differ at most twofold); 8: one
-// wavefront each; 9: hubs (one workgroup each; the host says from which degree on).  A hop that the 16-lane groups do not serve puts the
-// nodes of bins 3-7 into bin 8.
+// four nodes come from one bin, so their rows differ at most twofold); 8: one wavefront each;
+// 9: hubs (one workgroup each; the host says from which degree on).  A hop whose long rows the
+// 16-lane groups do not serve puts the nodes of bins 3-7 into bin 8.
 constexpr int kNumBins = 10;
 constexpr int kWideBin = 8, kHubBin = 9;
 constexpr uint32_t kGroupDegree = 2048;
@@ -78,22 +78,10 @@ __device__ __forceinline__ NodeRec* bin_rec(NodeRec* const* first, int bin, int6
 }
 
 // ---------------------------------------------------------------------------
-// block-wide helpers (256 threads = 4 waves)
+// block-wide helpers
 // ---------------------------------------------------------------------------
-// exclusive scan over the 256 threads of a block; *total receives the block sum
-__device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* lds4, uint32_t* total) {
-  const uint32_t in_wave = wave_excl_scan_u32(v);
-  const uint32_t w = threadIdx.x >> 6;
-  if (lane_id() == kWave - 1) lds4[w] = in_wave + v;
-  __syncthreads();
-  const uint32_t s0 = lds4[0], s1 = lds4[1], s2 = lds4[2], s3 = lds4[3];
-  __syncthreads();
-  const uint32_t before = (w > 0 ? s0 : 0) + (w > 1 ? s1 : 0) + (w > 2 ? s2 : 0);
-  *total = s0 + s1 + s2 + s3;
-  return before + in_wave;
-}
-
-// the same over a workgroup of kWide threads: lds holds one word per wavefront
+// exclusive scan over the kWide threads of a workgroup; lds holds one word per wavefront, *total
+// receives the workgroup's sum
 template <int kWide>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds, uint32_t* total) {
   constexpr int kWaves = kWide / kWave;

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kTileThreads) void k_flag(const IdxT* gid, const in
     }
   }
   uint32_t total;
-  uint32_t run = block_excl_scan_256(sum, lds4, &total);
+  uint32_t run = block_excl_scan<kTileThreads>(sum, lds4, &total);
 #pragma unroll
   for (int k = 0; k < kTilePerThread; ++k) {
     if (base_e + k < n) local_rank[base_e + k] = (int32_t)run;

@@ -45,7 +45,6 @@ struct SampleArgs {
   uint32_t force_radix;
 };
 
-// what a lane needs to write one sampled edge
 // Is node u's feature row in the device cache?  One bit per node (k_cached_bits): the lookups of
 // a neighbourhood are random, and a bitmap of N / 8 bytes stays in the L2 where the 4 N bytes of
 // the device map do not.  Ids outside the graph count as not cached (the emitter reports them).
@@ -82,11 +81,14 @@ struct Emitter {
 
 // How a launch of k_sample treats the weights:
 //   kUniform       all weights equal (no device map, or bias rate 1): the m largest draws;
-//   kWeightedFast  two weights; a wide node or hub is decided from the draws above the scan's
-//                  threshold alone where that is enough (at least m of them cached: the usual
-//                  case), and is put on a list for a second launch where it is not.  Keeps no
-//                  second candidate list, no rescanning path and so far fewer registers;
-//   kWeightedFull  two weights, every path: the second launch, which serves that list.
+//   kWeightedFast  two weights; a node of more than 32 neighbours is decided from the draws above the
+//                  scan's threshold alone where that is enough (at least m of them cached: the usual
+//                  case), and is marked for a second launch where it is not.  Keeps no second
+//                  candidate list, no rescanning path and so far fewer registers;
+//   kWeightedFull  two weights, every path: the second launch, which serves the marked nodes, or the
+//                  only one of the hop.
+constexpr int kUniform = 0, kWeightedFull = 1, kWeightedFast = 2;
+
 // the lane's index as a value that the compiler cannot trace back: what is computed from it stays where
 // it is used instead of being hoisted out of the node loop and held in registers for its whole length
 __device__ __forceinline__ uint32_t local_lane_id() {
@@ -94,8 +96,6 @@ __device__ __forceinline__ uint32_t local_lane_id() {
   asm volatile("" : "+v"(lane));
   return lane;
 }
-
-constexpr int kUniform = 0, kWeightedFull = 1, kWeightedFast = 2;
 
 constexpr double kInvOne = 1.0 / 65536.0;  // 1 / weight of an uncached neighbour (Q16.16)
 
@@ -532,9 +532,6 @@ __device__ __forceinline__ uint32_t second_list_floor(float keep, uint32_t bias_
   return kb >= 4294967040.0f ? 0u : 0u - (uint32_t)kb;
 }
 
-// cand [cap] and rest [m (+ 3 m + 2 xcap + capb when weighted)] are this wavefront's LDS buffers.
-// With prefiltered set, cand already holds pre_cnt candidates in slot order (a workgroup scanned
-// the row together; pre_cnt_b entries of the second list too) and the scan is skipped.
 // kWeightedFast: the node goes to the second launch.  A mark in its own record and no shared
 // list: a list needs a counter, and thousands of atomics on one word stall every wavefront
 // that touches the counter's cache line (0.2 ms per hop with a few thousand nodes left over).
@@ -542,6 +539,9 @@ __device__ __forceinline__ void defer_node(int32_t* left) {
   if (lane_id() == 0) *left = 1;
 }
 
+// A wavefront, one node.  cand [cap] and rest [m (+ 3 m + 2 xcap + capb when weighted)] are its LDS buffers.
+// With prefiltered set, cand already holds pre_cnt candidates in slot order (a workgroup scanned
+// the row together; pre_cnt_b entries of the second list too) and the scan is skipped.
 template <typename IdxT, int kMode>
 __device__ __forceinline__ void sample_node_wave(const SampleArgs<IdxT>& a, const int32_t* tile_offs,
                                  const NodeRec& r, int32_t n_dst, uint64_t* cand, uint64_t* rest,

@@ -142,8 +142,13 @@ uint32_t cap_for(uint32_t lambda) { return ((2 * lambda + 63) / 64) * 64; }
 // second launch a whole node's latency).
 // A weighted call whose first launches leave more than one node in kFullOnlyShare to the second
 // switches the next kFullOnlyCalls weighted calls of its context to a single full launch per
-// hop; after them the two-launch plan is tried again.  At that share the two plans cost about
-// the same (the first launch costs about three quarters of a full one on the same nodes).
+// hop; after them the two-launch plan is tried again.  Sampling by two launches and by one, us a
+// call of 16 384 seeds and three hops on 2.45 M nodes cached at random, by the share left over:
+//   bias rate 4:   3.5 %  906 / 978,  7.4 % 1 040 / 1 015,  14 % 1 203 / 1 052,  21 % 1 363 / 1 084
+//   bias rate 32:  3.6 % 1 342 / 1 640,  14 % 2 067 / 2 101,  21 % 2 393 / 2 273
+// They break even between 5 and 8 % at low bias rates (1 024 seeds: 2 %) and between 15 and 25 % at
+// high ones.  The line is on the side of the latter: beyond it one launch is as good at any rate, while
+// calls at low rates with shares in between keep a plan that costs up to 18 % (1 024 seeds: 30 %) more.
 constexpr int64_t kFullOnlyShare = 5;
 constexpr int kFullOnlyCalls = 16;
 uint32_t lambda_for_first_list(int32_t m) { return (uint32_t)(m + 6.0 * std::sqrt((double)m) + 12.0); }
@@ -173,9 +178,9 @@ uint32_t challenger_cap(int32_t fanout, uint32_t capb) {
 }
 
 // The 16-lane groups keep a list of kListCap = 64 candidates per node.  Fewer than m or more than 64
-// send a node to the wavefront path, which costs about ten times a group's share: rarer than one in a
-// thousand up to fanout 20, one in a hundred at 32 (weighted lists are longer, for enough of them
-// has to be cached).
+// send a node to the wavefront path, which costs about ten times a group's share: one in two thousand
+// at most up to fanout 20, one in a hundred at 30, one in fifty at 32 (of rows of 2 048; weighted lists
+// are longer, for enough of them has to be cached, and at most one in 350 fails at fanout 16).
 // They serve frontiers that fill the chip with a quarter of a wavefront per node.  In smaller ones a
 // wavefront per node has the shorter chain: hop 0 of 1 024 nodes with fanout 25 takes 11.8 us with
 // wavefronts and 15.5 with groups, of 4 096 (weighted) 20.1 and 23.2; hop 1 of some 20 k nodes
@@ -197,7 +202,7 @@ uint32_t group_lambda_for(int32_t m, bool weighted) {
 uint32_t sample_lds_entries(uint32_t cap, int32_t fanout, bool weighted, uint32_t capb) {
   uint32_t entries = cap + (uint32_t)fanout;
   if (weighted) entries += 3 * (uint32_t)fanout + 2 * challenger_cap(fanout, capb) + capb;
-  return (std::max<uint32_t>(entries, a3::kGroupLdsEntries) + 1u) & ~1u;  // the lists are read 16 bytes at a time
+  return std::max<uint32_t>(entries, a3::kGroupLdsEntries);
 }
 
 // the first record of a bin (see a3::bin_rec)
