@@ -26,9 +26,9 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E bandwidth
 # plain integer ALU peak: 256 CUs x 64 lanes x 2.4 GHz 32-bit lane-operations per second
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # lane-operations the method needs per scanned neighbour slot: a quarter of a Philox4x32-10 block
-# (20 32x32->64 multiplies at a quarter of the 32-bit rate = 80, plus 20 three-way xors) and one
-# comparison of the draw
-OPS_PER_SLOT = (20 * 4 + 20) / 4 + 1
+# (20 32x32->64 multiplies and 20 three-way xors; 64 blocks take a SIMD 200 cycles, measured, which is the
+# time of 50 operations: the multiplies run at the 32-bit rate) and one comparison of the draw
+OPS_PER_SLOT = 200 / 4 / 4 + 1
 HEADLINE = "citation"
 OTHERS = ["social", "copurchase"]
 METRIC = "sampled edges/s + feature-gather GB/s (% of HBM peak) per mini-batch, 1 GPU"
